@@ -26,8 +26,8 @@ __device__ __noinline__ ElbmF64Result elbm_alpha_fp64(ElbmF64Site s, double eps,
   }
   ElbmParams<double> e64{eps, 0.0, dS_cut, max_iter, norm, fallback};
   ElbmF64Result r;
-  r.alpha = (float)elbm_alpha<double, Q>(fd, qd, Dd, alpha_max<double, Q>(fd, Dd), e64,
-                                         r.branch, r.iters);
+  r.alpha = (float)elbm_alpha<double, Q>(fd, qd, Dd, nullptr, 0.0, alpha_max<double, Q>(fd, Dd),
+                                         false, e64, r.branch, r.iters);
   return r;
 }
 
@@ -88,9 +88,12 @@ static __device__ ElbmGroupResult elbm_alpha_fp64_group(double f_c, double q_c, 
   const double nrm = norm == 0 ? sqrt(U) : group16_sum(fabs(D));
   const double s1 = group16_sum(D * lnr);
   const double amax = group16_min(D < 0.0 ? f / (-D) : __builtin_huge_val());
-  bool probe = amax < __builtin_huge_val();
+  // A root exists iff S_f(alpha_max) < 0.  The first iterate's tangent (S_f is
+  // concave with S_f(0) = 0) settles that for most sites; the others probe
+  // alpha_max next and resume from the saved evaluation.
+  bool need_probe = amax < __builtin_huge_val(), probe = false;
   double a = amax > 2.0 ? 2.0 : 0.5 * (1.0 + amax);
-  double prev = __builtin_huge_val();
+  double prev = __builtin_huge_val(), sf_a = 0.0, d1_a = 0.0, d2_a = 0.0;
   constexpr double kNoise = 64.0 * 2.220446049250313e-16;
   for (int it = 0;;) {
     const double aa = probe ? amax : a;
@@ -99,15 +102,28 @@ static __device__ ElbmGroupResult elbm_alpha_fp64_group(double f_c, double q_c, 
     const double s0 = group16_sum(f * h_log<double>(xa, l));
     const double t1 = group16_sum(D * (l + lnr));
     const double t2 = group16_sum(D * D / (f + aa * D));
-    const double sf = -s0 - aa * s1, d1 = -t1, d2 = -t2;
+    double sf = -s0 - aa * s1, d1 = -t1, d2 = -t2;
     if (probe) {
       if (sf >= 0.0) {
         r.alpha = fallback == 0 ? amax : 1.0;
         r.branch = EB_NOROOT;
         return r;
       }
-      probe = false;
-      continue;
+      probe = need_probe = false;
+      sf = sf_a;
+      d1 = d1_a;
+      d2 = d2_a;
+    } else if (need_probe) {
+      const double gap = amax - a;
+      if (d1 < 0.0 && gap >= 0.25 * a && sf + 0.5 * d1 * gap < 0.0) {
+        need_probe = false;
+      } else {
+        sf_a = sf;
+        d1_a = d1;
+        d2_a = d2;
+        probe = true;
+        continue;
+      }
     }
     const double step_est = fabs(sf / d1);
     const bool stalled = it >= 2 && step_est >= 0.5 * prev && step_est < kNoise * a;
@@ -180,7 +196,9 @@ struct CollInfo {
 // (LBGK omega, MRT shear rate s_nu, ELBM 2 beta).
 // DEFER (FP32 ELBM only): a site that needs the FP64 solve is not collided;
 // ci.deferred is set and post[] is left unset (k_elbm_f64 rebuilds it).
-template <class S, int Q, int COLL, bool DEFER = false>
+// SHORT (FP32 ELBM): most sites are near equilibrium (large periodic
+// lattices; beside walls the extra tests cost 2 % of the step).
+template <class S, int Q, int COLL, bool DEFER = false, bool SHORT = false>
 __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::R>& A,
                                              const typename StoreT<S>::R v[Q],
                                              const typename StoreT<S>::R feq[Q],
@@ -217,12 +235,35 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
       fa[i] = v[i] + sh;
       qa[i] = feq[i] + sh;
     }
-    const R amax = alpha_max<R, Q>(fa, d);
     int br = EB_ROOT;
     R alpha;
     ElbmParams<R> ep{A.eps, A.atol, A.dS_cut, A.max_iter, A.norm, A.fallback};
     bool f64 = false;
+    // m = max |D_i| / f_i
+    R rf[Q], m = R(0), fmin_ = fa[0];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      fmin_ = fmin(fmin_, fa[i]);
+      if constexpr (sizeof(R) == 4) {
+        rf[i] = rcp<R>(fa[i]);
+        m = fmax(m, fabs(d[i]) * rf[i]);
+      } else {
+        rf[i] = d[i] / fa[i];
+        m = fmax(m, fabs(rf[i]));
+      }
+    }
     if constexpr (sizeof(R) == 4) {
+      // alpha_max >= 1/m, which settles every test against alpha_max near
+      // equilibrium without its nine quotients
+      bool lower = false;
+      R amax;
+      if constexpr (SHORT) {
+        lower = fmin_ > R(0) && m * fmax(A.f64_below, R(4)) < R(0.9999);
+        if (lower) amax = R(0.9999) * rcp<R>(m);
+        else amax = alpha_max<R, Q>(fa, d);
+      } else {
+        amax = alpha_max<R, Q>(fa, d);
+      }
       if (amax < A.f64_below) {
         if constexpr (DEFER) {
           ci.deferred = true;
@@ -242,10 +283,13 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
         ci.iters = r.iters;
         f64 = true;
       } else {
-        alpha = elbm_alpha<R, Q>(fa, qa, d, amax, ep, br, ci.iters);
+        alpha = elbm_alpha<R, Q, SHORT>(fa, qa, d, rf, m, amax, lower, ep, br, ci.iters);
       }
     } else {
-      alpha = elbm_alpha<R, Q>(fa, qa, d, amax, ep, br, ci.iters);
+      if (fmin_ > R(0) && m < kElbmNear)
+        alpha = elbm_alpha_near<Q>(qa, d, rf, A.dS_cut, br, ci.iters);
+      else
+        alpha = elbm_alpha<R, Q>(fa, qa, d, rf, m, alpha_max<R, Q>(fa, d), false, ep, br, ci.iters);
     }
     const R ab = alpha * (om * R(0.5));
 #pragma unroll
@@ -320,7 +364,7 @@ __device__ __forceinline__ void selected_state(const StepArgs<typename StoreT<S>
 // of the wavefront calls it.
 // DEFER (FP32 ELBM): sites whose root solve needs FP64 are listed for
 // k_elbm_f64 instead of being collided, limited and stored here.
-template <class S, int Q, int COLL, bool EHR = true, bool DEFER = false>
+template <class S, int Q, int COLL, bool EHR = true, bool DEFER = false, bool SHORT = false>
 __device__ __forceinline__ void site_finish(const StepArgs<typename StoreT<S>::R>& A, int x, int y,
                                             bool valid, bool wall, long long region,
                                             typename StoreT<S>::R v[Q],
@@ -351,7 +395,7 @@ __device__ __forceinline__ void site_finish(const StepArgs<typename StoreT<S>::R
   if (valid && !wall) {
     const R om = A.omega_field ? A.omega_field[(long long)y * A.pitch + x] : A.omega;
     CollInfo<R> ci;
-    collide_site<S, Q, COLL, DEFER>(A, v, feq, d, om, post, ci);
+    collide_site<S, Q, COLL, DEFER, SHORT>(A, v, feq, d, om, post, ci);
     deferred = ci.deferred;
     if constexpr (COLL == COLL_ELBM) {
       // a deferred site counts no event here (its CollInfo is the default)

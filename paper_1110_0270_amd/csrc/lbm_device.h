@@ -183,6 +183,12 @@ template <> __device__ __forceinline__ float lg1p_series<float>(float x) {
   return p * x;
 }
 template <> __device__ __forceinline__ double lg1p_series<double>(double x) { return log1p(x); }
+// |x| < 2^-8: the terms to x^4 (the next is below 5e-11 relative, under half
+// a unit in the last place).
+__device__ __forceinline__ float lg1p_series_short(float x) {
+  return fmaf(fmaf(fmaf(-1.0f / 4.0f, x, 1.0f / 3.0f), x, -1.0f / 2.0f), x, 1.0f) * x;
+}
+constexpr float kShortSeries = 0x1p-8f;
 template <> __device__ __forceinline__ float lg1p<float>(float x) {
   const float ser = lg1p_series<float>(x);
   const float u = 1.0f + x;
@@ -237,26 +243,52 @@ __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 
 // S_f and its derivatives at alpha = a.  s1 = sum_i D_i ln(f_i / f*_i), the
 // same for every alpha.  With r_i = D_i / (f_i + a D_i) the higher
-// derivatives are S_f^(2) = -sum D r, S_f^(3) = sum D r^2 and
-// S_f^(4) = -2 sum D r^3 (d2, d3, d4); rmax = max |r_i| bounds the ratio of
-// consecutive terms of the Taylor series of S_f in alpha around a.
+// derivatives are S_f^(n+1) = (-1)^n (n-1)! T_n, T_n = sum D_i r_i^n, n >= 1;
+// rmax = max |r_i| bounds the ratio of consecutive terms of the Taylor series
+// of S_f in alpha around a.  FP32 keeps T_1..T_3, FP64 T_1..T_10.
 // m = max_i |D_i| / f_i (FP32; from rf): a m < 0.0999999 guarantees every
 // computed |x_i| = |fl(fl(a D_i) rf_i)| < 0.1 (the margin of 1e-6 covers
-// the two roundings), so that the wavefront can take the series alone.
-template <class R, int Q>
+// the two roundings), so that the wavefront can take the series alone;
+// below 2^-8 it takes their first terms.
+// SHORT (FP32): the kernel expects resolved flows and carries the short
+// series.
+template <class R> struct ElbmSeries { static constexpr int T = sizeof(R) == 4 ? 3 : 10; };
+template <class R, int Q, bool SHORT>
 __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[Q], R s1, R m,
-                                         R a, R& sf, R& d1, R& d2, R& d3, R& d4, R& rmax) {
-  R s0 = R(0), t1 = R(0), t2 = R(0), t3 = R(0), t4 = R(0);
+                                         R a, R& sf, R& d1, R T[ElbmSeries<R>::T], R& rmax) {
+  constexpr int NT = ElbmSeries<R>::T;
+  R s0 = R(0), t1 = R(0);
+#pragma unroll
+  for (int n = 0; n < NT; ++n) T[n] = R(0);
   rmax = R(0);
   auto higher = [&](int i) {
-    const R r = D[i] * rcp<R>(f[i] + a * D[i]);
-    const R u = D[i] * r, u2 = u * r;
-    t2 += u;
-    t3 += u2;
-    t4 += u2 * r;
-    rmax = fmax(rmax, fabs(r));
+    if constexpr (sizeof(R) == 4) {
+      const R r = D[i] * rcp<R>(f[i] + a * D[i]);
+      const R u = D[i] * r, u2 = u * r;
+      T[0] += u;
+      T[1] += u2;
+      T[2] += u2 * r;
+      rmax = fmax(rmax, fabs(r));
+    } else {
+      const R r = D[i] / (f[i] + a * D[i]);
+      R u = D[i];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        u *= r;
+        T[n] += u;
+      }
+      rmax = fmax(rmax, fabs(r));
+    }
   };
-  if (sizeof(R) == 4 && wave_all(a * m < R(0.0999999))) {
+  if (SHORT && wave_all(a * m < R(kShortSeries))) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const R x = over_f<R>(a * D[i], f[i], rf[i]);
+      s0 += f[i] * ((R)h_poly_short((float)x) * x * x);
+      t1 += D[i] * (R)lg1p_series_short((float)x);
+      higher(i);
+    }
+  } else if (sizeof(R) == 4 && wave_all(a * m < R(0.0999999))) {
     // every |x_i| < 0.1 on the wavefront: ln(1 + x) and h(x) are their
     // series, the values the selects below would keep
 #pragma unroll
@@ -274,18 +306,21 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
       const R l = lg1p<R>(xl);
       s0 += f[i] * h_log<R>(x, l);
       t1 += D[i] * l;
-      if constexpr (sizeof(R) == 4) {
-        higher(i);
-      } else {
-        t2 += fdiv<R>(D[i] * D[i], f[i] + a * D[i]);
-      }
+      higher(i);
     }
   }
   sf = -s0 - a * s1;
   d1 = -(t1 + s1);
-  d2 = -t2;
-  d3 = t3;
-  d4 = R(-2) * t4;
+}
+
+// Largest alpha keeping f + alpha D >= 0 (inf if no D_i < 0).
+template <class R, int Q>
+__device__ __forceinline__ R alpha_max(const R f[Q], const R D[Q]) {
+  R amax = r_inf<R>();
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+    if (D[i] < R(0)) amax = fmin(amax, fdiv<R>(f[i], -D[i]));
+  return amax;
 }
 
 template <class R>
@@ -308,22 +343,25 @@ struct ElbmParams {
 // inequality), so sum f*_i x_i^2 / (2 (1 + max x/3)) <= Delta S decides it
 // for every other site.  The same x_i give ln(f_i / f*_i) and the entropic
 // norm.
-template <class R, int Q>
-__device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
-                        const ElbmParams<R>& p, int& branch, int& iters) {
+// FP32: rf = rcp(f), m = max_i |D_i| / f_i.  `lower` says that amax is only a
+// lower bound of alpha_max; the exact value is taken where the bound does not
+// settle a decision (the decisions, and so alpha, are those of the exact one).
+template <class R, int Q, bool SHORT = false>
+__device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q], R m, R amax,
+                        bool lower, const ElbmParams<R>& p, int& branch, int& iters) {
   iters = 0;
   bool nonpos = false;
 #pragma unroll
   for (int i = 0; i < Q; ++i) nonpos |= (f[i] <= R(0));
   if (nonpos) { branch = EB_NONPOS; return R(1); }
   R x[Q], U = R(0), xmax = R(-1);
-  bool xsmall = true;
+  R xabs = R(0);
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     x[i] = fdiv<R>(-D[i], feq[i]);
     U += feq[i] * x[i] * x[i];
     xmax = fmax(xmax, x[i]);
-    xsmall &= fabs(x[i]) < R(0.1);
+    xabs = fmax(xabs, fabs(x[i]));
   }
   if (U < R(2) * p.dS_cut * (R(1) + xmax / R(3))) {
     R dS = R(0);
@@ -333,7 +371,10 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
   }
   // s1 = sum_i D_i ln(f_i / f*_i), ln(f_i / f*_i) = ln(1 + x_i)
   R s1 = R(0);
-  if (sizeof(R) == 4 && wave_all(xsmall)) {
+  if (SHORT && wave_all(xabs < R(kShortSeries))) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) s1 += D[i] * (R)lg1p_series_short((float)x[i]);
+  } else if (sizeof(R) == 4 && wave_all(xabs < R(0.1))) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) s1 += D[i] * lg1p_series<R>(x[i]);
   } else {
@@ -347,12 +388,6 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
 #pragma unroll
     for (int i = 0; i < Q; ++i) nrm += fabs(D[i]);
   }
-  R rf[Q], m = R(0);
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    rf[i] = sizeof(R) == 4 ? rcp<R>(f[i]) : R(0);
-    m = fmax(m, fabs(D[i]) * rf[i]);
-  }
   // One evaluation site for S_f and its derivatives (the kernel's code size
   // decides its speed).  A root exists iff S_f(alpha_max) < 0 (alpha_max
   // finite).  S_f is concave (S is concave, f + alpha D affine) with
@@ -363,15 +398,23 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
   // next evaluation is the probe at alpha_max, after which the iteration
   // resumes from the saved first one.  The evaluation that stops the
   // iteration also serves the final sign check.
-  // FP32: after a full evaluation at c, S_f and its first two derivatives at
-  // c + dl come from the Taylor series in alpha to the fourth derivative
-  // while |dl| rmax <= 2^-10 (the first omitted term is below 1e-9 of the
-  // second-order one, under FP32 rounding); further away, a full evaluation.
-  constexpr bool TAYLOR = sizeof(R) == 4;
+  // After a full evaluation at c, S_f and its first two derivatives at
+  // c + dl come from the Taylor series in alpha; further away than the bound
+  // below, a full evaluation.  FP32: to the fourth derivative while
+  // |dl| rmax <= 2^-10 (the first omitted term is below 1e-9 of the
+  // second-order one, under FP32 rounding).  FP64: to the eleventh while
+  // |dl| rmax <= 2^-5 (omitted: below 2^-50 of the second-order term); the
+  // logarithms of a second and third evaluation bound the walls' wavefronts
+  // (256^2 cavity).
+  constexpr int NT = ElbmSeries<R>::T;
+  constexpr R kReach = sizeof(R) == 4 ? R(0x1p-10) : R(0x1p-5);
   bool need_probe = amax < r_inf<R>();
   bool saved = false, full = true;
   R a = amax > R(2) ? R(2) : R(0.5) * (R(1) + amax);
-  R c = a, F0 = R(0), F1 = R(0), F2 = R(0), F3 = R(0), F4 = R(0), rmax = r_inf<R>();
+  R c = a, F0 = R(0), F1 = R(0), rmax = r_inf<R>();
+  R T[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) T[n] = R(0);
   R prev = r_inf<R>();
   // a Newton step within 64 units in the last place of alpha that no longer
   // halves is rounding noise: the iteration has converged as far as this
@@ -382,8 +425,8 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
     R sf, d1, d2;
     const bool probing = need_probe && saved;
     if (full || probing) {
-      R e0, e1, e2, e3, e4, em;
-      sf_parts<R, Q>(f, rf, D, s1, m, probing ? amax : a, e0, e1, e2, e3, e4, em);
+      R e0, e1, eT[NT], em;
+      sf_parts<R, Q, SHORT>(f, rf, D, s1, m, probing ? amax : a, e0, e1, eT, em);
       if (probing) {
         if (e0 >= R(0)) {
           branch = EB_NOROOT;
@@ -392,17 +435,28 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
         need_probe = false;   // resume at a = c
         sf = F0;
         d1 = F1;
-        d2 = F2;
+        d2 = -T[0];
       } else {
         c = a;
-        F0 = e0; F1 = e1; F2 = e2; F3 = e3; F4 = e4;
+        F0 = e0;
+        F1 = e1;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) T[n] = eT[n];
         rmax = em;
         sf = e0;
         d1 = e1;
-        d2 = e2;
+        d2 = -eT[0];
         if (need_probe) {
-          const R gap = amax - a;
-          if (d1 < R(0) && gap >= R(0.25) * a && sf + R(0.5) * d1 * gap < R(0)) {
+          R gap = amax - a;
+          bool proved = d1 < R(0) && gap >= R(0.25) * a && sf + R(0.5) * d1 * gap < R(0);
+          if (SHORT && lower && !proved) {
+            amax = alpha_max<R, Q>(f, D);
+            lower = false;
+            gap = amax - a;
+            proved = !(amax < r_inf<R>()) ||
+                     (d1 < R(0) && gap >= R(0.25) * a && sf + R(0.5) * d1 * gap < R(0));
+          }
+          if (proved) {
             need_probe = false;   // the tangent proves the root
           } else {
             saved = true;
@@ -410,11 +464,27 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
           }
         }
       }
-    } else {
+    } else if constexpr (sizeof(R) == 4) {
+      const R F2 = -T[0], F3 = T[1], F4 = R(-2) * T[2];
       const R dl = a - c;
       sf = F0 + dl * (F1 + dl * (R(0.5) * F2 + dl * (F3 * R(1.0 / 6.0) + dl * (F4 * R(1.0 / 24.0)))));
       d1 = F1 + dl * (F2 + dl * (R(0.5) * F3 + dl * (F4 * R(1.0 / 6.0))));
       d2 = F2 + dl * (F3 + dl * (R(0.5) * F4));
+    } else {
+      // S_f   = F0 + dl F1 + sum (-1)^n T_n dl^(n+1) / (n (n + 1))
+      // S_f'  = F1 + sum (-1)^n T_n dl^n / n,  S_f'' = sum (-1)^n T_n dl^(n-1)
+      const R dl = a - c;
+      R q0 = R(0), q1 = R(0), q2 = R(0);
+#pragma unroll
+      for (int n = NT; n >= 1; --n) {
+        const R t = (n & 1) ? -T[n - 1] : T[n - 1];
+        q0 = fma(q0, dl, t * (R(1) / R(n * (n + 1))));
+        q1 = fma(q1, dl, t * (R(1) / R(n)));
+        q2 = fma(q2, dl, t);
+      }
+      sf = F0 + dl * (F1 + dl * q0);
+      d1 = F1 + dl * q1;
+      d2 = q2;
     }
     const R step_est = fabs(fdiv<R>(sf, d1));
     const bool stalled = it >= 2 && step_est >= R(0.5) * prev && step_est < kNoise * a;
@@ -428,23 +498,82 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], R amax,
     R disc = d1 * d1 - R(2) * sf * d2;
     R delta = disc >= R(0) ? fdiv<R>(R(2) * sf, -d1 + sqrt(disc)) : fdiv<R>(-sf, d1);
     R an = a + delta;
+    if (SHORT && lower && an >= amax) {
+      amax = alpha_max<R, Q>(f, D);
+      lower = false;
+    }
     if (an >= amax) an = R(0.5) * (a + amax);
     if (an <= R(1)) an = R(0.5) * (a + R(1));
     a = an;
-    full = !TAYLOR || !(fabs(a - c) * rmax <= R(0x1p-10));
+    full = !(fabs(a - c) * rmax <= kReach);
   }
   branch = EB_ROOT;
   return a;
 }
 
-// Largest alpha keeping f + alpha D >= 0 (inf if no D_i < 0).
-template <class R, int Q>
-__device__ __forceinline__ R alpha_max(const R f[Q], const R D[Q]) {
-  R amax = r_inf<R>();
+// FP64 root near equilibrium, max |r_i| = |D_i| / f_i below 2^-5.  With the
+// moments M_n = sum_i D_i r_i^n,
+//   S_f(alpha) / alpha = sum_n (-1)^(n+1) M_n (1/n - alpha^n / (n (n + 1))),
+// whose n = 1 coefficient vanishes at alpha = 2 (M_2 = O(r M_1)): the root is
+// 2 + O(r).  Twelve moments (truncation below 1e-16), Newton's step from 2
+// with the second-order term of the series inversion, which leaves O(r^4),
+// and two Newton steps on the polynomial: one division and 24 operations per
+// component instead of nine logarithms per evaluation.  (The FP32 forms keep
+// the iteration below: with 16-bit storage any change in alpha's last bits
+// changes roundings that spread over the lattice.)  A root exists here:
+// alpha_max >= 1 / max |r_i| > 32 and S_f is concave.  The cutoff test is
+// elbm_alpha's own sum wherever M_1, which is 2 Delta S to within 2 max |r_i|,
+// does not clear it.  r = D / f, with every f_i > 0.
+constexpr double kElbmNear = 0.03125;
+template <int Q>
+__device__ __forceinline__ double elbm_alpha_near(const double feq[Q], const double D[Q],
+                                                  const double r[Q], double dS_cut, int& branch,
+                                                  int& iters) {
+  constexpr int N = 12;
+  double M[N];
 #pragma unroll
-  for (int i = 0; i < Q; ++i)
-    if (D[i] < R(0)) amax = fmin(amax, fdiv<R>(f[i], -D[i]));
-  return amax;
+  for (int n = 0; n < N; ++n) M[n] = 0.0;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    double u = D[i];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      u *= r[i];
+      M[n] += u;
+    }
+  }
+  if (M[0] * 0.45 < dS_cut) {
+    double dS = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < Q; ++i) dS += feq[i] * h_fn<double>(-D[i] / feq[i]);
+    if (dS < dS_cut) {
+      branch = EB_CUTOFF;
+      iters = 0;
+      return 2.0;
+    }
+  }
+  branch = EB_ROOT;
+  iters = 1;
+  const double F0 = M[1] * (1.0 / 6.0) - M[2] * (1.0 / 3.0) + M[3] * 0.55;
+  const double F1 = M[1] * (2.0 / 3.0) - M[0] * 0.5 - M[2] + M[3] * 1.6;
+  const double G = M[1] * (1.0 / 6.0) - M[2] * 0.5 + M[3] * 1.2;
+  const double e = -F0 / F1;
+  double a = 2.0 + (e - G / F1 * e * e);
+  double s0 = 0.0;
+#pragma unroll
+  for (int n = 1; n <= N; ++n) s0 += ((n & 1) ? 1.0 : -1.0) / (double)n * M[n - 1];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    double p = 0.0, q = 0.0;   // S_f / alpha = s0 + a p, its derivative q
+#pragma unroll
+    for (int n = N; n >= 1; --n) {
+      const double c = (n & 1) ? -1.0 : 1.0;
+      p = fma(p, a, c / (double)(n * (n + 1)) * M[n - 1]);
+      q = fma(q, a, c / (double)(n + 1) * M[n - 1]);
+    }
+    a -= fma(a, p, s0) / q;
+  }
+  return a;
 }
 
 }  // namespace lbm

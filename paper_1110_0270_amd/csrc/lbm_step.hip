@@ -384,9 +384,9 @@ __global__ __launch_bounds__(256, (COLL == COLL_LBGK && sizeof(S) == 2) ? 8 : 1)
                      ? site_dS_dev<R, Q, SH>(v, d, m0, A.rho0, dx, dy, dx, screen)
                      : R(0);
     const long long region = ((long long)y * A.tiles_x + tile_x) * 4 + threadIdx.x / 64;
-    site_finish<S, Q, COLL, EHR, COLL == COLL_ELBM && sizeof(R) == 4>(A, x, y, valid, false, region,
-                                                                       v, feq, d, m0, ux, uy, dS, fr,
-                                                                       cnt);
+    constexpr bool E32 = COLL == COLL_ELBM && sizeof(R) == 4;
+    site_finish<S, Q, COLL, EHR, E32, E32>(A, x, y, valid, false, region, v, feq, d, m0, ux, uy, dS,
+                                           fr, cnt);
   }
 }
 
