@@ -163,28 +163,21 @@ __device__ __forceinline__ void adjoint_site(const StepArgs<typename StoreT<S>::
     if (COLL == COLL_MRT || mrt_here) {
       // q = p + B (f* - p), B = Minv diag(rates(omega)) M; the rates of the
       // presets depend on the shear rate too
-      R z[Q], m[Q];
+      if constexpr (Q == 9) {
+        R z[Q], m[Q], w[Q];
+        mrt_mul<R, true, true>(A.mrt_basis, lq, z);
+        mrt_mul<R, false, false>(A.mrt_basis, d, m);
 #pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        R sz = R(0), sm = R(0);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          sz += A.Minv[i * Q + k] * lq[i];
-          sm += A.M[k * Q + i] * d[i];
+        for (int k = 0; k < Q; ++k) {
+          gw += mrt_drate<R>(A, k, om) * z[k] * m[k];
+          z[k] *= mrt_rate<R>(A, k, om);
         }
-        z[k] = sz;
-        m[k] = sm;
-        gw += mrt_drate<R>(A, k, om) * sz * sm;
-      }
+        mrt_mul<R, false, true>(A.mrt_basis, z, w);
 #pragma unroll
-      for (int k = 0; k < Q; ++k) z[k] *= mrt_rate<R>(A, k, om);
-#pragma unroll
-      for (int j = 0; j < Q; ++j) {
-        R w = R(0);
-#pragma unroll
-        for (int k = 0; k < Q; ++k) w += A.M[k * Q + j] * z[k];
-        mu[j] = lq[j] - w;
-        lf[j] += w;
+        for (int j = 0; j < Q; ++j) {
+          mu[j] = lq[j] - w[j];
+          lf[j] += w[j];
+        }
       }
     } else if constexpr (COLL == COLL_LBGK) {
       // q = p + omega (f* - p)

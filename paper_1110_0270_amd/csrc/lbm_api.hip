@@ -175,7 +175,7 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
     L.off_hist = take((size_t)kHistWords * 4);
     L.off_coarse = take(kCoarse * 4);
     L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
-    // kSweepRegions regions x 64 entries per k_fix_regions workgroup
+    // kSweepRegions regions x 64 entries per sweep workgroup
     L.off_stage = take((size_t)((tiles * 4 + kSweepRegions - 1) / kSweepRegions) * kSweepRegions * 64 * 4);
     L.bcap = std::min<long long>(L.cap, 1ll << 20);
     L.off_blist = take((size_t)L.bcap * 4);
@@ -200,41 +200,6 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
 }
 
 double omega_of(const lbm_config* c) { return c->nu >= 0 ? 1.0 / (3.0 * c->nu + 0.5) : c->omega; }
-
-// MRT change of basis (section 5), rebuilt from its velocity polynomials in
-// tensor order; inverse by Gauss-Jordan elimination with partial pivoting.
-void mrt_matrices(int basis, double M[81], double Minv[81]) {
-  for (int i = 0; i < 9; ++i) {
-    const double vx = (i % 3) - 1, vy = (i / 3) - 1, v2 = vx * vx + vy * vy;
-    double r[9];
-    if (basis == LBM_MRT_M1) {
-      r[0] = 1; r[1] = -4 + 3 * v2; r[2] = 4 - 10.5 * v2 + 4.5 * v2 * v2; r[3] = vx;
-      r[4] = (-5 + 3 * v2) * vx; r[5] = vy; r[6] = (-5 + 3 * v2) * vy; r[7] = vx * vx - vy * vy;
-      r[8] = vx * vy;
-    } else {
-      r[0] = 1; r[1] = vx; r[2] = vy; r[3] = v2; r[4] = vx * vx - vy * vy; r[5] = vx * vy;
-      r[6] = vx * vx * vy; r[7] = vx * vy * vy; r[8] = vx * vx * vy * vy;
-    }
-    for (int k = 0; k < 9; ++k) M[k * 9 + i] = r[k];
-  }
-  double a[9][18];
-  for (int r = 0; r < 9; ++r)
-    for (int c = 0; c < 18; ++c) a[r][c] = c < 9 ? M[r * 9 + c] : (c - 9 == r ? 1.0 : 0.0);
-  for (int c = 0; c < 9; ++c) {
-    int p = c;
-    for (int r = c + 1; r < 9; ++r) if (std::fabs(a[r][c]) > std::fabs(a[p][c])) p = r;
-    if (p != c) for (int k = 0; k < 18; ++k) std::swap(a[p][k], a[c][k]);
-    const double piv = a[c][c];
-    for (int k = 0; k < 18; ++k) a[c][k] /= piv;
-    for (int r = 0; r < 9; ++r) {
-      if (r == c) continue;
-      const double f = a[r][c];
-      if (f != 0.0) for (int k = 0; k < 18; ++k) a[r][k] -= f * a[c][k];
-    }
-  }
-  for (int r = 0; r < 9; ++r)
-    for (int c = 0; c < 9; ++c) Minv[r * 9 + c] = a[r][c + 9];
-}
 
 template <class R>
 void fill_args(StepArgs<R>& A, const lbm_config* c, const Layout& L, char* ws) {
@@ -271,9 +236,7 @@ void fill_args(StepArgs<R>& A, const lbm_config* c, const Layout& L, char* ws) {
   // an LBGK lattice (section 5)
   A.sel_mrt = c->sel_action == LBM_SEL_MRT ? 1 : 0;
   if (c->collision == LBM_MRT || A.sel_mrt) {
-    double M[81], Mi[81];
-    mrt_matrices(c->mrt_basis, M, Mi);
-    for (int i = 0; i < 81; ++i) { A.M[i] = (R)M[i]; A.Minv[i] = (R)Mi[i]; }
+    A.mrt_basis = c->mrt_basis == LBM_MRT_M1 ? 0 : 1;
     double rates[9];
     if (c->mrt_basis == LBM_MRT_M1) {
       // rows rho, e, epsilon, j_x, q_x, j_y, q_y, p_xx, p_xy

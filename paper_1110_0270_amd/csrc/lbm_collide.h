@@ -3,6 +3,7 @@
 // of them take bit-identical branches.
 #pragma once
 
+#include "lbm_mrt.h"
 #include "lbm_site.h"
 
 namespace lbm {
@@ -212,21 +213,13 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
 #pragma unroll
     for (int i = 0; i < Q; ++i) post[i] = v[i] + om * d[i];
   } else if constexpr (COLL == COLL_MRT) {
-    R m[Q];
+    R m[Q], s[Q];
+    mrt_mul<R, false, false>(A.mrt_basis, d, m);
 #pragma unroll
-    for (int k = 0; k < Q; ++k) {
-      R s = R(0);
+    for (int k = 0; k < Q; ++k) m[k] *= mrt_rate<R>(A, k, om);
+    mrt_mul<R, true, false>(A.mrt_basis, m, s);
 #pragma unroll
-      for (int j = 0; j < Q; ++j) s += A.M[k * Q + j] * d[j];
-      m[k] = s * mrt_rate<R>(A, k, om);
-    }
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      R s = R(0);
-#pragma unroll
-      for (int k = 0; k < Q; ++k) s += A.Minv[i * Q + k] * m[k];
-      post[i] = v[i] + s;
-    }
+    for (int i = 0; i < Q; ++i) post[i] = v[i] + s[i];
   } else {  // ELBM
     R fa[Q], qa[Q];
 #pragma unroll

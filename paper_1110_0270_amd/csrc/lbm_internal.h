@@ -117,8 +117,7 @@ struct StepArgs {
   R lid[9];              // moving-wall term 6 w_i rho_wall (v_i . u_wall)
   R lid_u;               // lid speed of the diffusive wall
   // MRT (moment space): F = f + Minv (rates .* (M (f* - f)))
-  R M[81];
-  R Minv[81];
+  int mrt_basis;         // 0 M1, 1 M2
   R rates[9];
   unsigned nu_rows;      // bit mask of rows whose rate is the shear rate
   unsigned q_rows;       // rows whose rate is a function q_mode of the shear rate
