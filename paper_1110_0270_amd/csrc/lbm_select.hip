@@ -7,23 +7,30 @@
 // The step kernel appends only sites whose key (the bit pattern of Delta S)
 // is at least a floor carried over from the previous step, and counts them
 // in a 4096-bucket histogram whose frame also comes from the previous step.
-// Selection then touches the short candidate list only:
-//   k_fb_scan   counts the candidates in every workgroup; unless a rescan
-//               is needed, its first workgroup finds the boundary bucket
-//               (holding the k-th largest key) from the histogram and the
-//               others return.  Only when the candidates cannot hold the
-//               answer (fewer than k above a raised floor) all of them
-//               rescan the lattice, histogram the top 12 bits of Delta S
-//               and pick a floor bin that holds at least k sites;
-//   k_fb_append same condition: rescans and appends from that bin up;
-//               its last workgroup then finds the boundary bucket;
-//   k_fix_regions writes f* at candidates above the boundary bucket and
-//               lists those inside it;
-//   k_fix_tail  resolves the boundary bucket exactly by an MSD radix select
-//               on (key descending, site index ascending), sets the next
-//               step's floor and frame, and resets the counters;
+// Selection then touches the short candidate list only, in two launches:
+//   k_sel_sweep every workgroup takes the candidate count and the boundary
+//               bucket (holding the k-th largest key) from the counters and
+//               the histogram, writes f* at its regions' candidates above
+//               that bucket and lists those inside it.  Only when the
+//               candidates cannot hold the answer (fewer than k above a
+//               raised floor) the workgroups rescan the lattice instead,
+//               histogram the top 12 bits of Delta S and pick a floor bin
+//               that holds at least k sites;
+//   k_sel_tail  one workgroup resolves the boundary bucket exactly by an MSD
+//               radix select on (key descending, site index ascending), sets
+//               the next step's floor and frame, and resets the counters.
+//               After a rescan its workgroups first append the sites from
+//               the floor bin up, and the last of them sweeps all regions;
+//   k_sel_one   lattices of one sweep workgroup (65536 sites at most): all of
+//               it in one launch of one workgroup;
 //   k_sel_mrt   (MRT limiter only) replaces f* at the selected sites by the
 //               MRT collision.
+// A launch costs 4 to 6 us of a step here (latency, not work): with the
+// decision, the append and the sweep in kernels of their own the selection
+// took 28.6 us of a 4096^2 FP32 step (kernel medians), in two launches 22.1;
+// BF16 39.8 -> 32.1.
+#include <algorithm>
+
 #include "lbm_collide.h"
 
 namespace lbm {
@@ -66,40 +73,51 @@ __device__ __forceinline__ bool last_block(unsigned int* ticket) {
   return is_last;
 }
 
-// Block-wide search of an LDS histogram h[0..NB) from the top bin down: *bin
-// receives the bin where the running count first reaches `need` (-1 if the
-// histogram holds fewer), *above the count in the bins above it.  Every
-// thread of the block calls it (blockDim.x a multiple of 64, at most 1024).
-// Thread t sums a contiguous run of bins from the top; the running counts
-// come from a shuffle scan in each wavefront plus the wavefront totals.
-template <int NB>
-__device__ void find_from_top(const unsigned int* h, unsigned long long need, int* bin,
+// LDS position of bin b of a 4096-bin histogram: one word of padding per 128
+// bins, so that a wavefront that loads words of the global histogram in
+// order (bins 128 apart, see hist_pos) stores them to different banks.
+__device__ __forceinline__ int hx(int b) { return b + (b >> 7); }
+constexpr int kHistLds = kBuckets + kBuckets / 128;
+
+// Block-wide search of an LDS histogram of NB bins (bin b at h[hx(b)] when
+// PAD, else h[b]) from the top bin down: *bin receives the bin where the
+// running count first reaches `need` (-1 if the histogram holds fewer),
+// *above the count in the bins above it.  Every thread of the block calls it
+// (blockDim.x a multiple of 64, at most 1024; the counts sum to less than
+// 2^31, the limit on the lattice's sites).  Thread t sums a contiguous run of
+// bins from the top; the running counts come from a shuffle scan in each
+// wavefront plus the wavefront totals.
+template <int NB, bool PAD>
+__device__ void find_from_top(const unsigned int* h, unsigned long long need64, int* bin,
                               unsigned long long* above) {
-  __shared__ unsigned long long wsum[16];
+  __shared__ unsigned int wsum[16];
   __shared__ int s_bin;
-  __shared__ unsigned long long s_above;
+  __shared__ unsigned int s_above;
+  const unsigned int need = need64 < 0x80000000ull ? (unsigned int)need64 : 0x80000000u;
   const int T = blockDim.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int C = (NB + T - 1) / T;
   const int hi = NB - t * C;
   const int lo = hi - C > 0 ? hi - C : 0;
-  unsigned long long s = 0;
-  for (int b = lo; b < hi; ++b) s += h[b];
-  unsigned long long incl = s;
+  auto at_bin = [&](int b) { return h[PAD ? hx(b) : b]; };
+  unsigned int s = 0;
+  for (int b = lo; b < hi; ++b) s += at_bin(b);
+  unsigned int incl = s;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long v = __shfl_up(incl, o);
+    const unsigned int v = __shfl_up(incl, o);
     if (lane >= o) incl += v;
   }
   if (lane == 63) wsum[wv] = incl;
   if (t == 0) { s_bin = -1; s_above = 0; }
   __syncthreads();
   for (int j = 0; j < wv; ++j) incl += wsum[j];
-  const unsigned long long excl = incl - s;
+  const unsigned int excl = incl - s;
   if (s > 0 && need > 0 && excl < need && need <= incl) {
-    unsigned long long c = excl;
+    unsigned int c = excl;
     for (int b = hi - 1; b >= lo; --b) {
-      if (c + h[b] >= need) { s_bin = b; s_above = c; break; }
-      c += h[b];
+      const unsigned int n = at_bin(b);
+      if (c + n >= need) { s_bin = b; s_above = c; break; }
+      c += n;
     }
   }
   __syncthreads();
@@ -141,88 +159,121 @@ __device__ __forceinline__ unsigned long long candidate_count(const unsigned lon
   return n;
 }
 
+// This step's candidate count and boundary bucket (-1: take every candidate,
+// kBuckets: none), and the count of the candidates above it.
+struct Boundary {
+  long long nc;
+  int bin;
+  unsigned long long above;
+};
+
 // The bucket holding the k-th largest candidate key, from the step's
-// histogram (in LDS) and candidate count; stored in the selection state
-// for the region sweep.  Every thread of one workgroup calls it.
-template <class R>
-__device__ void boundary_from(const unsigned int* h, long long nc, long long k, SelState* st) {
-  int boundary = -1;
-  unsigned long long above = 0;
+// histogram (in LDS) and candidate count.  Every thread of the workgroup
+// calls it.
+__device__ __forceinline__ Boundary boundary_from(const unsigned int* h, long long nc, long long k) {
+  Boundary b{nc, -1, 0ull};
   if (k <= 0) {
-    boundary = kBuckets;                 // take nothing
+    b.bin = kBuckets;                    // take nothing
   } else if (nc > k) {
-    find_from_top<kBuckets>(h, (unsigned long long)k, &boundary, &above);
-    if (boundary < 0) boundary = -1;
+    find_from_top<kBuckets, true>(h, (unsigned long long)k, &b.bin, &b.above);
   }
+  return b;
+}
+__device__ __forceinline__ void store_boundary(const Boundary& b, SelState* st) {
   if (threadIdx.x == 0) {
-    st->b_bin = boundary;
-    st->b_nc = (unsigned long long)nc;
-    st->b_above = above;
+    st->b_bin = b.bin;
+    st->b_nc = (unsigned long long)b.nc;
+    st->b_above = b.above;
   }
 }
 
-// calibrate = 0: the step's first selection kernel; 1: first floor of a
-// freshly set lattice.
-template <class S, int Q>
-__global__ __launch_bounds__(1024) void k_fb_scan(const StepArgs<typename StoreT<S>::R> A,
-                                                 long long k, unsigned int* coarse,
-                                                 int calibrate) {
-  using R = typename StoreT<S>::R;
-  SelState* st = A.sel;
-  static_assert(kCoarse == kBuckets, "one LDS histogram serves both uses");
-  __shared__ unsigned int h[kCoarse];
-  if (!calibrate) {
-    // Every workgroup takes the same decision from the same counters.  The
-    // first one loads the histogram with them (one memory round trip) and,
-    // unless the step rescans, finds the boundary bucket.
-    __shared__ unsigned long long s_nc;
-    if (blockIdx.x == 0)
-      for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) h[i] = ld_rlx(&A.hist[hist_pos(i)]);
-    if (threadIdx.x < 64) {
-      const unsigned long long n = candidate_count(A.ccount);
-      if (threadIdx.x == 0) s_nc = n;
-    }
-    const unsigned long long step = st->step;
-    const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
-    const bool raised = ((step & 1ull) ? fr1 : fr0) != 0;
-    __syncthreads();
-    // a rescan is needed when the floor was raised and fewer than k sites
-    // reached it
-    const long long nc = (long long)s_nc;
-    if (!(nc < k && raised)) {
-      if (blockIdx.x == 0) boundary_from<R>(h, nc, k, st);
-      return;
-    }
-    __syncthreads();
+// The step's histogram into LDS, in the order of its words (whole cache
+// lines per wavefront; loading bin by bin touched 64 lines per load, which
+// took 7 us of a launch).
+__device__ __forceinline__ void load_hist(const unsigned int* hist, unsigned int* h) {
+  for (int p = threadIdx.x; p < kBuckets; p += blockDim.x)
+    h[hx(128 * (p % 32) + p / 32)] = hist[p];
+}
+// The step's histogram (when h is given) and candidate count; the loads issue
+// together, and the values are complete after the barrier at the end.
+template <class R>
+__device__ __forceinline__ long long load_counts(const StepArgs<R>& A, unsigned int* h) {
+  __shared__ unsigned long long s_nc;
+  if (h) load_hist(A.hist, h);
+  if (threadIdx.x < 64) {
+    const unsigned long long n = candidate_count(A.ccount);
+    if (threadIdx.x == 0) s_nc = n;
   }
-  for (int i = threadIdx.x; i < kCoarse; i += blockDim.x) h[i] = 0;
   __syncthreads();
-  const long long n = (long long)A.nx * A.ny;
-  for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(s / A.nx), x = (int)(s % A.nx);
-    R v[Q], feq[Q], d[Q], m0, ux, uy;
-    const R dS = site_prep<S, Q>(A, x, y, v, feq, d, m0, ux, uy, true);
-    if (dS > A.ehr_delta) atomicAdd(&h[coarse_bin((float)dS)], 1u);
+  return (long long)s_nc;
+}
+
+// Delta S of site (x, y) as the step kernel sees it, with the branch-free
+// pull on periodic lattices (the same values).
+template <class S, int Q>
+__device__ __forceinline__ typename StoreT<S>::R scan_dS(const StepArgs<typename StoreT<S>::R>& A,
+                                                         int x, int y, typename StoreT<S>::R screen,
+                                                         typename StoreT<S>::R& m0,
+                                                         typename StoreT<S>::R& ux,
+                                                         typename StoreT<S>::R& uy) {
+  using R = typename StoreT<S>::R;
+  R v[Q], feq[Q], d[Q];
+  if (A.bc == BC_PERIODIC) return site_prep<S, Q, true, false>(A, x, y, v, feq, d, m0, ux, uy, true, screen);
+  return site_prep<S, Q>(A, x, y, v, feq, d, m0, ux, uy, true, screen);
+}
+
+// Rescan, first half: the coarse histogram (top 12 bits of Delta S) of the
+// eligible sites of the workgroup's share of tiles, added to `coarse`.  The
+// workgroup takes tiles in the step kernel's layout, four at a time (no
+// division per site), and wavefront-aggregated LDS atomics (a shear layer's
+// sites crowd into few bins): 4096^2 FP32 550 -> 196 us, and a step that
+// rescans 1.1 -> 0.7 ms.
+template <class S, int Q>
+__device__ void scan_sites(const StepArgs<typename StoreT<S>::R>& A, unsigned int* h,
+                           unsigned int* coarse, int wg, int nwg) {
+  using R = typename StoreT<S>::R;
+  for (int i = threadIdx.x; i < kHistLds; i += blockDim.x) h[i] = 0;
+  __syncthreads();
+  const int T = A.tiles_x * A.tiles_y;
+  const int w = threadIdx.x / 64, lane = threadIdx.x % 64, per = (int)blockDim.x / 256;
+  for (int t = wg * per + w / 4; t < T; t += nwg * per) {
+    int x, y;
+    tile_site(t, w % 4, lane, A.tiles_x, A.tile_tx, x, y);
+    bool on = x < A.nx && y < A.ny;
+    unsigned int bin = 0;
+    if (on) {
+      R m0, ux, uy;
+      const R dS = scan_dS<S, Q>(A, x, y, R(0), m0, ux, uy);
+      on = dS > A.ehr_delta;
+      bin = (unsigned int)hx((int)coarse_bin((float)dS));
+    }
+    hist_add(h, bin, on);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kCoarse; i += blockDim.x)
-    if (h[i]) atomicAdd(&coarse[i], h[i]);
-  if (!last_block(&st->ticket)) return;
-  // The coarse bin that holds the k-th largest Delta S, and the frame of the
-  // fallback candidates' histogram.
-  for (int i = threadIdx.x; i < kCoarse; i += blockDim.x) h[i] = ld_rlx(&coarse[i]);
+    if (h[hx(i)]) atomicAdd(&coarse[i], h[hx(i)]);
+}
+
+// After every workgroup's scan_sites, by one workgroup: the coarse bin that
+// holds the k-th largest Delta S and the frame of the fallback candidates'
+// histogram (calibrate: the first floor of a freshly set lattice, at the
+// 3k-th); clears the step's histogram and counters for the append.
+template <class R>
+__device__ void pick_floor_bin(const StepArgs<R>& A, long long k, unsigned int* h,
+                               unsigned int* coarse, bool calibrate) {
+  SelState* st = A.sel;
+  for (int i = threadIdx.x; i < kCoarse; i += blockDim.x) h[hx(i)] = ld_rlx(&coarse[i]);
   __syncthreads();
   int b;
   unsigned long long above;
   const unsigned long long want = calibrate ? 3ull * (unsigned long long)k : (unsigned long long)k;
-  find_from_top<kCoarse>(h, want > 0 ? want : 1ull, &b, &above);
+  find_from_top<kCoarse, true>(h, want > 0 ? want : 1ull, &b, &above);
   if (b < 0) b = 0;                                   // fewer eligible sites: take all
   __shared__ int top;
   if (threadIdx.x == 0) top = 0;
   __syncthreads();
   for (int i = threadIdx.x; i < kCoarse - 16; i += blockDim.x)   // highest finite bin
-    if (h[i]) atomicMax(&top, i);
+    if (h[hx(i)]) atomicMax(&top, i);
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long edge = coarse_edge_key<R>(b);
@@ -245,7 +296,6 @@ __global__ __launch_bounds__(1024) void k_fb_scan(const StepArgs<typename StoreT
       st->base_key[par] = edge;
       st->shift[par] = frame_shift(edge, coarse_edge_key<R>(top + 1));
     }
-    st->ticket = 0;
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kCoarse; i += blockDim.x) coarse[i] = 0;
@@ -253,63 +303,43 @@ __global__ __launch_bounds__(1024) void k_fb_scan(const StepArgs<typename StoreT
   for (int i = threadIdx.x; i < kCountSlots; i += blockDim.x) A.ccount[i * kCountStride] = 0;
 }
 
-template <class R>
-__device__ void find_boundary(const StepArgs<R>& A, long long k) {
-  __shared__ unsigned int h[kBuckets];
-  __shared__ unsigned long long s_nc;
-  for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) h[i] = ld_rlx(&A.hist[hist_pos(i)]);
-  if (threadIdx.x < 64) {
-    const unsigned long long n = candidate_count(A.ccount);
-    if (threadIdx.x == 0) s_nc = n;
-  }
-  __syncthreads();
-  boundary_from<R>(h, (long long)s_nc, k, A.sel);
-}
-
-// Rescan append, in the step kernel's tile layout so that every wavefront
-// region is rewritten (stale counts of the step kernel included).
+// Rescan, second half: appends the sites from the floor bin up, in the step
+// kernel's tile layout so that every wavefront region is rewritten (stale
+// counts of the step kernel included).  Sites provably below the bin's edge
+// skip the exact Delta S.
 template <class S, int Q>
-__global__ __launch_bounds__(256) void k_fb_append(const StepArgs<typename StoreT<S>::R> A,
-                                                   long long k) {
+__device__ void append_sites(const StepArgs<typename StoreT<S>::R>& A, int wg, int nwg) {
   using R = typename StoreT<S>::R;
-  SelState* st = A.sel;
-  if (!st->fallback) return;
+  const SelState* st = A.sel;
   const unsigned int fb = (unsigned int)st->fb_bin;
+  const R screen = value_of_key<R>(coarse_edge_key<R>((int)fb));
+  StepFrame fr = step_frame(st);
   const int T = A.tiles_x * A.tiles_y;
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  for (int t = blockIdx.x; t < T; t += gridDim.x) {
+  const int w = threadIdx.x / 64, lane = threadIdx.x % 64, per = (int)blockDim.x / 256;
+  for (int t = wg * per + w / 4; t < T; t += nwg * per) {
     int x, y;
-    tile_site(t, w, lane, A.tiles_x, A.tile_tx, x, y);
-    const bool valid = x < A.nx && y < A.ny;
+    tile_site(t, w % 4, lane, A.tiles_x, A.tile_tx, x, y);
     bool is_c = false;
     R dS = R(0), m0 = R(0), ux = R(0), uy = R(0);
-    if (valid) {
-      R v[Q], feq[Q], d[Q];
-      dS = site_prep<S, Q>(A, x, y, v, feq, d, m0, ux, uy, true);
+    if (x < A.nx && y < A.ny) {
+      dS = scan_dS<S, Q>(A, x, y, screen, m0, ux, uy);
       is_c = (dS > A.ehr_delta) && coarse_bin((float)dS) >= fb;
     }
-    const long long region = (long long)t * 4 + w;
-    const unsigned long long mask = __ballot(is_c);
-    if (lane == 0) {
-      A.wcount[region] = (uint32_t)__popcll(mask);
-      if (mask)
-        atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
-    }
-    if (is_c) {
-      const long long pos = region * 64 + __popcll(mask & ((1ull << lane) - 1ull));
-      A.cand_key[pos] = key_of<R>(dS);
-      A.cand_idx[pos] = (uint32_t)(y * A.nx + x);
-      A.cand_mom[pos] = m0;
-      A.cand_mom[A.cap + pos] = ux;
-      A.cand_mom[2 * A.cap + pos] = uy;
-      const int par = (int)(st->step & 1ull);
-      atomicAdd(&A.hist[hist_pos(bucket_of<R>((unsigned long long)key_of<R>(dS), st->base_key[par], st->shift[par]))], 1u);
-    }
+    const long long region = (long long)t * 4 + w % 4;
+    if (lane == 0 && !__ballot(is_c)) A.wcount[region] = 0;
+    append_candidates<R>(A, fr, region, is_c, key_of<R>(dS), (uint32_t)(y * A.nx + x), m0, ux, uy);
   }
-  if (last_block(&st->ticket)) {
-    find_boundary<R>(A, k);
-    if (threadIdx.x == 0) st->ticket = 0;
-  }
+}
+
+// The first floor of a freshly set lattice.
+template <class S, int Q>
+__global__ __launch_bounds__(1024) void k_sel_calibrate(const StepArgs<typename StoreT<S>::R> A,
+                                                        long long k, unsigned int* coarse) {
+  __shared__ unsigned int h[kHistLds];
+  scan_sites<S, Q>(A, h, coarse, blockIdx.x, gridDim.x);
+  if (!last_block(&A.sel->ticket)) return;
+  pick_floor_bin<typename StoreT<S>::R>(A, k, h, coarse, true);
+  if (threadIdx.x == 0) A.sel->ticket = 0;
 }
 
 // f* of site idx from the moments recorded with its candidate entry,
@@ -345,6 +375,18 @@ __device__ __forceinline__ unsigned int lds_slot(bool on, unsigned int* ctr) {
 // up to kTailRank entries are ranked directly.
 constexpr int kTailStage = 2048;
 constexpr int kTailRank = 256;
+// LDS staging of a sweep workgroup: selected sites and boundary entries (the
+// rest, up to kSweepRegions x 64 entries, go to its global stage).
+constexpr int kRegSel = 6144;
+constexpr int kRegBnd = 2048;
+// The sweep's and the tail's LDS, in turn.
+union SelScratch {
+  struct { int32_t sel[kRegSel], bnd[kRegBnd]; } sweep;
+  struct {
+    unsigned long long off[kTailStage];
+    uint32_t ni[kTailStage], p[kTailStage];
+  } tail;
+};
 
 // Exact resolution of the boundary bucket and the next step's floor and
 // frame, by one workgroup.
@@ -352,16 +394,18 @@ template <class S, int Q>
 __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, long long n_sites,
                          int32_t* selected, uint32_t* blist, long long bcap,
                          long long* n_sel_out, int32_t* tape_sel, long long* tape_cnt,
-                         long long tape_len, uint32_t* scratch, long long scratch_len) {
+                         long long tape_len, uint32_t* scratch, long long scratch_len,
+                         const Boundary& bd, unsigned long long sel_bnd, unsigned int* h,
+                         bool have_h, SelScratch& lds) {
   using R = typename StoreT<S>::R;
   SelState* st = A.sel;
-  __shared__ unsigned int h[kBuckets];
   __shared__ unsigned int dh[256];
   __shared__ unsigned long long s_off_pref;
   __shared__ uint32_t s_idx_pref;
   __shared__ unsigned int s_tot;
-  __shared__ unsigned long long t_off[kTailStage];
-  __shared__ uint32_t t_ni[kTailStage], t_p[kTailStage];
+  auto& t_off = lds.tail.off;
+  auto& t_ni = lds.tail.ni;
+  auto& t_p = lds.tail.p;
   // every load is issued before the first barrier; both parities' fields
   // are loaded with the step count (one round trip)
   const unsigned long long step = st->step;
@@ -369,13 +413,10 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   const unsigned int shift_p[2] = {st->shift[0], st->shift[1]};
   const int raised_p[2] = {st->floor_raised[0], st->floor_raised[1]};
   const unsigned long long floor_p[2] = {st->floor_key[0], st->floor_key[1]};
-  for (int i = threadIdx.x; i < kBuckets; i += blockDim.x) h[i] = ld_rlx(&A.hist[hist_pos(i)]);
-  // candidate count, boundary bucket and the count above it, as found by
-  // k_fb_scan (or by the rescan's last workgroup)
-  const long long nc = (long long)st->b_nc;
-  const int b_bin = st->b_bin;
-  const unsigned long long b_above = st->b_above;
-  const unsigned long long sel_bnd = st->sel_bnd;
+  if (!have_h) load_hist(A.hist, h);
+  const long long nc = bd.nc;
+  const int b_bin = bd.bin;
+  const unsigned long long b_above = bd.above;
   const long long m_all = (long long)(sel_bnd & 0xffffffffull);
   // state the epilogue updates
   const bool fell_back = st->fallback != 0;
@@ -572,7 +613,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
       }
       int dsel;
       unsigned long long dabove;
-      find_from_top<256>(dh, need_left, &dsel, &dabove);
+      find_from_top<256, false>(dh, need_left, &dsel, &dabove);
       if (dsel < 0) dsel = 0;
       need_left -= dabove;
       if (threadIdx.x == 0) {
@@ -667,7 +708,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     } else {
       int t2;
       unsigned long long a2;
-      find_from_top<kBuckets>(h, 3ull * (unsigned long long)k, &t2, &a2);
+      find_from_top<kBuckets, true>(h, 3ull * (unsigned long long)k, &t2, &a2);
       if (t2 >= 0 && t2 < kBuckets - 1) fnext = base + ((unsigned long long)t2 << shift);
       else if (t2 < 0) fnext = base > 2 * KeyTraits<R>::quarter ? base - 2 * KeyTraits<R>::quarter : 0ull;
       else fnext = floor_prev;
@@ -682,7 +723,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   {
     int tmax = -1;
     for (int i = threadIdx.x; i < kBuckets; i += blockDim.x)
-      if (h[i]) tmax = i;
+      if (h[hx(i)]) tmax = i;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       const int v = __shfl_xor(tmax, o);
@@ -715,72 +756,97 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   for (int i = threadIdx.x; i < kCountSlots; i += blockDim.x) A.ccount[i * kCountStride] = 0;
 }
 
-// LDS staging of a k_fix_regions workgroup: selected sites and boundary
-// entries (the rest, up to kSweepRegions x 64 entries, go to its global
-// stage).
-constexpr int kRegSel = 6144;
-constexpr int kRegBnd = 2048;
 // Regions with at most this many candidates are walked lane by lane.
 constexpr int kFewCand = 4;
 
-// Selection: k_fix_regions sends every candidate above the boundary bucket to
-// equilibrium and lists the boundary bucket; k_fix_tail (one workgroup of
-// 1024: the exact resolution is a chain of dependent loads over the list)
-// resolves the boundary bucket exactly and prepares the next step.
+// One candidate entry p (when `on`): writes f* if it lies above the boundary
+// bucket (sel); bnd says that it lies inside.  Returns its site.
 template <class S, int Q>
-__global__ __launch_bounds__(kSweepRegions) void k_fix_regions(const StepArgs<typename StoreT<S>::R> A,
-                                                     long long k, int32_t* selected,
-                                                     int32_t* stage, uint32_t* blist,
-                                                     long long bcap, int32_t* tape_sel,
-                                                     long long tape_len) {
+__device__ __forceinline__ uint32_t visit_entry(const StepArgs<typename StoreT<S>::R>& A, bool on,
+                                                long long p, int boundary, unsigned long long base,
+                                                unsigned int shift, bool& sel, bool& bnd) {
   using R = typename StoreT<S>::R;
+  sel = bnd = false;
+  if (!on) return 0u;
+  // the whole entry in one round trip
+  const unsigned long long key = (unsigned long long)A.cand_key[p];
+  const uint32_t idx = A.cand_idx[p];
+  const R m0 = A.cand_mom[p], ux = A.cand_mom[A.cap + p], uy = A.cand_mom[2 * A.cap + p];
+  const int b = bucket_of<R>(key, base, shift);
+  sel = boundary < 0 || b > boundary;
+  bnd = b == boundary;
+  if (sel) write_feq_at<S, Q>(A, idx, m0, ux, uy);
+  return idx;
+}
+
+// The candidates of 64 regions, lane j's region r holding cnt of them: visit(on,
+// p) for every entry p, called by every lane of the wavefront.  Sparse regions
+// (at most kFewCand entries, where candidates are scattered over the lattice)
+// are walked by their own lane, all lanes at once; dense regions (candidates
+// crowding into the rows of a shear layer) one after another with one lane
+// per entry.
+template <class F>
+__device__ __forceinline__ void walk_regions(long long r, uint32_t cnt, F visit) {
+  const int lane = __lane_id();
+  const uint32_t few = cnt <= (uint32_t)kFewCand ? cnt : 0u;
+  uint32_t fmax_c = few;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const uint32_t v = __shfl_xor(fmax_c, o);
+    fmax_c = v > fmax_c ? v : fmax_c;
+  }
+  for (uint32_t e = 0; e < fmax_c; ++e) visit(e < few, r * 64 + e);
+  unsigned long long nz = __ballot(cnt > (uint32_t)kFewCand);
+  while (nz) {
+    const int j = __ffsll((long long)nz) - 1;
+    nz &= nz - 1;
+    const uint32_t c = __shfl(cnt, j);
+    const long long rj = __shfl(r, j);
+    visit((uint32_t)lane < c, rj * 64 + lane);
+  }
+}
+
+// The regions of sweep chunk c of nchunk (kSweepRegions regions, one per
+// thread of the workgroup): f* at the candidates above the boundary bucket,
+// whose sites join the selected list, and the boundary bucket's entries into
+// blist.
+// 64 regions per wavefront, spread over the whole lattice with a stride of
+// the wavefront count (candidates crowd into whole rows of a shear layer;
+// a contiguous assignment would hand one wavefront an entire dense row).
+constexpr int kSweepWaves = kSweepRegions / 64;
+__device__ __forceinline__ long long sweep_region(int c, int nchunk) {
+  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
+  return (long long)lane * nchunk * kSweepWaves + (long long)c * kSweepWaves + w;
+}
+struct TailArgs {
+  long long k, n_sites;
+  int32_t* selected;
+  uint32_t* blist;
+  long long bcap;
+  long long* n_sel_out;
+  int32_t* tape_sel;
+  long long* tape_cnt;
+  long long tape_len;
+  int32_t* stage;
+  unsigned int* coarse;
+  int nchunk;
+};
+template <class S, int Q>
+__device__ void sweep_chunk(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a, int c,
+                            uint32_t cnt, const Boundary& bd, const StepFrame& fr,
+                            int32_t* selected, SelScratch& lds) {
   SelState* st = A.sel;
   __shared__ unsigned int s_sel, s_bnd;
   __shared__ unsigned long long s_base_sel, s_base_bnd;
-  __shared__ int32_t l_sel[kRegSel], l_bnd[kRegBnd];
-  // both parities' frames are loaded with the step count (one round trip)
-  const unsigned long long step = st->step;
-  const unsigned long long base0 = st->base_key[0], base1 = st->base_key[1];
-  const unsigned int shift0 = st->shift[0], shift1 = st->shift[1];
-  const int boundary = st->b_bin;          // -1: take every candidate
-  const long long tape_t = st->tape_t;
-  if (tape_sel && tape_t < tape_len) selected = tape_sel + tape_t * k;
-  const unsigned long long base = (step & 1ull) ? base1 : base0;
-  const unsigned int shift = (step & 1ull) ? shift1 : shift0;
+  auto& l_sel = lds.sweep.sel;
+  auto& l_bnd = lds.sweep.bnd;
   if (threadIdx.x == 0) { s_sel = 0; s_bnd = 0; }
   __syncthreads();
-  // 64 regions per wavefront, spread over the whole lattice with a stride of
-  // the wavefront count (candidates crowd into whole rows of a shear layer;
-  // a contiguous assignment would hand one wavefront an entire dense row).
-  // One read of the 64 counts, then the non-empty regions in turn with one
-  // lane per entry.
-  const long long nreg = (long long)A.tiles_x * A.tiles_y * 4;
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  constexpr int kWaves = kSweepRegions / 64;
-  const long long g = (long long)blockIdx.x * kWaves + w, nwave = (long long)gridDim.x * kWaves;
-  const long long my_r = (long long)lane * nwave + g;
-  int32_t* my_stage = stage + (long long)blockIdx.x * kSweepRegions * 64;
-  uint32_t cnt = 0;
-  if (my_r < nreg) cnt = A.wcount[my_r];
-  // One candidate entry p (when `on`): f* at the selected, staging of the
-  // selected and of the boundary entries.  Every lane of the wavefront calls
-  // it (the LDS slots come from ballots).
-  auto visit = [&](bool on, long long p) {
-    bool sel = false, bnd = false;
-    uint32_t idx = 0;
-    R m0 = R(0), ux = R(0), uy = R(0);
-    if (on) {
-      // the whole entry in one round trip
-      const unsigned long long key = (unsigned long long)A.cand_key[p];
-      idx = A.cand_idx[p];
-      m0 = A.cand_mom[p];
-      ux = A.cand_mom[A.cap + p];
-      uy = A.cand_mom[2 * A.cap + p];
-      const int b = bucket_of<R>(key, base, shift);
-      sel = boundary < 0 || b > boundary;
-      bnd = b == boundary;
-    }
-    if (sel) write_feq_at<S, Q>(A, idx, m0, ux, uy);
+  const long long my_r = sweep_region(c, a.nchunk);
+  int32_t* my_stage = a.stage + (long long)c * kSweepRegions * 64;
+  walk_regions(my_r, cnt, [&](bool on, long long p) {
+    bool sel, bnd;
+    const uint32_t idx = visit_entry<S, Q>(A, on, p, bd.bin, fr.base, fr.shift, sel, bnd);
     // staged in LDS, or past its capacity in the workgroup's global stage
     const unsigned int slot = lds_slot(sel, &s_sel);
     if (sel) {
@@ -792,27 +858,7 @@ __global__ __launch_bounds__(kSweepRegions) void k_fix_regions(const StepArgs<ty
       if (q < (unsigned int)kRegBnd) l_bnd[q] = (int32_t)p;
       else my_stage[kSweepRegions * 64 - 1 - q] = (int32_t)p;
     }
-  };
-  // Sparse regions (at most kFewCand entries, where candidates are scattered
-  // over the lattice) are walked by their own lane, all lanes at once; dense
-  // regions (candidates crowding into the rows of a shear layer) one after
-  // another with one lane per entry.
-  const uint32_t few = cnt <= (uint32_t)kFewCand ? cnt : 0u;
-  uint32_t fmax_c = few;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const uint32_t v = __shfl_xor(fmax_c, o);
-    fmax_c = v > fmax_c ? v : fmax_c;
-  }
-  for (uint32_t e = 0; e < fmax_c; ++e) visit(e < few, my_r * 64 + e);
-  unsigned long long nz = __ballot(cnt > (uint32_t)kFewCand);
-  while (nz) {
-    const int j = __ffsll((long long)nz) - 1;
-    nz &= nz - 1;
-    const uint32_t c = __shfl(cnt, j);
-    const long long rj = __shfl(my_r, j);
-    visit((uint32_t)lane < c, rj * 64 + lane);
-  }
+  });
   if (cnt) A.wcount[my_r] = 0;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -826,29 +872,172 @@ __global__ __launch_bounds__(kSweepRegions) void k_fix_regions(const StepArgs<ty
   }
   __syncthreads();
   for (unsigned int i = threadIdx.x; i < s_sel; i += blockDim.x)
-    if ((long long)(s_base_sel + i) < k)
+    if ((long long)(s_base_sel + i) < a.k)
       selected[s_base_sel + i] = i < (unsigned int)kRegSel ? l_sel[i] : my_stage[i];
   for (unsigned int i = threadIdx.x; i < s_bnd; i += blockDim.x)
-    if ((long long)(s_base_bnd + i) < bcap)
-      blist[s_base_bnd + i] = (uint32_t)(i < (unsigned int)kRegBnd ? l_bnd[i] : my_stage[kSweepRegions * 64 - 1 - i]);
+    if ((long long)(s_base_bnd + i) < a.bcap)
+      a.blist[s_base_bnd + i] = (uint32_t)(i < (unsigned int)kRegBnd ? l_bnd[i] : my_stage[kSweepRegions * 64 - 1 - i]);
+}
+
+// The whole region sweep by one workgroup (small lattices, and the step after
+// a rescan): its LDS counters are the lists' slots.  Returns both counts
+// (SelState::sel_bnd's layout).
+template <class S, int Q>
+__device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a,
+                                        const Boundary& bd, const StepFrame& fr, int32_t* selected) {
+  __shared__ unsigned int s_sel, s_bnd;
+  if (threadIdx.x == 0) { s_sel = 0; s_bnd = 0; }
+  __syncthreads();
+  constexpr int U = 8;                     // region counts in flight per thread
+  // a wavefront's regions lie a wavefront count apart (dense neighbours go to
+  // different wavefronts)
+  const int mine = (int)(threadIdx.x % 64) * (int)(blockDim.x / 64) + (int)(threadIdx.x / 64);
+  const long long nreg = (long long)A.tiles_x * A.tiles_y * 4;
+  for (long long r0 = 0; r0 < nreg; r0 += (long long)U * blockDim.x) {
+    uint32_t cnt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long r = r0 + (long long)u * blockDim.x + mine;
+      cnt[u] = r < nreg ? A.wcount[r] : 0u;
+    }
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+      uint32_t c = cnt[0];
+#pragma unroll
+      for (int q = 1; q < U; ++q) c = u == q ? cnt[q] : c;
+      if (!__ballot(c != 0)) continue;
+      const long long r = r0 + (long long)u * blockDim.x + mine;
+      walk_regions(r, c, [&](bool on, long long p) {
+        bool sel, bnd;
+        const uint32_t idx = visit_entry<S, Q>(A, on, p, bd.bin, fr.base, fr.shift, sel, bnd);
+        const unsigned int slot = lds_slot(sel, &s_sel);
+        if (sel && (long long)slot < a.k) selected[slot] = (int32_t)idx;
+        const unsigned int q = lds_slot(bnd, &s_bnd);
+        if (bnd && (long long)q < a.bcap) a.blist[q] = (uint32_t)p;
+      });
+      if (c) A.wcount[r] = 0;
+    }
+  }
+  __syncthreads();
+  return ((unsigned long long)s_sel << 32) | s_bnd;
 }
 
 template <class S, int Q>
-__global__ __launch_bounds__(1024) void k_fix_tail(const StepArgs<typename StoreT<S>::R> A,
-                                                   long long k, long long n_sites,
-                                                   int32_t* selected, uint32_t* blist,
-                                                   long long bcap, long long* n_sel_out,
-                                                   int32_t* tape_sel, long long* tape_cnt,
-                                                   long long tape_len, uint32_t* scratch,
-                                                   long long scratch_len) {
-  fix_tail<S, Q>(A, k, n_sites, selected, blist, bcap, n_sel_out, tape_sel, tape_cnt, tape_len,
-                 scratch, scratch_len);
+__device__ __forceinline__ void tail_of(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a,
+                                        const Boundary& bd, unsigned long long sel_bnd,
+                                        unsigned int* h, bool have_h, SelScratch& lds) {
+  // the region sweep's stage (one entry per candidate slot) serves as the
+  // exact resolution's scratch
+  fix_tail<S, Q>(A, a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
+                 a.tape_cnt, a.tape_len, (uint32_t*)a.stage,
+                 (long long)a.nchunk * kSweepRegions * 64, bd, sel_bnd, h, have_h, lds);
+}
+
+__device__ __forceinline__ int32_t* selected_slot(const TailArgs& a, const SelState* st) {
+  const long long t = st->tape_t;
+  return a.tape_sel && t < a.tape_len ? a.tape_sel + t * a.k : a.selected;
+}
+
+// First launch: the sweep, or the rescan's scan.
+template <class S, int Q>
+__global__ __launch_bounds__(kSweepRegions) void k_sel_sweep(const StepArgs<typename StoreT<S>::R> A,
+                                                             const TailArgs a) {
+  using R = typename StoreT<S>::R;
+  SelState* st = A.sel;
+  static_assert(kCoarse == kBuckets, "one LDS histogram serves both uses");
+  __shared__ unsigned int h[kHistLds];
+  __shared__ SelScratch lds;
+  // every load is issued before the first barrier
+  const bool sweeps = (int)blockIdx.x < a.nchunk;
+  const long long my_r = sweep_region(blockIdx.x, a.nchunk);
+  const uint32_t cnt =
+      sweeps && my_r < (long long)A.tiles_x * A.tiles_y * 4 ? A.wcount[my_r] : 0u;
+  const StepFrame fr = step_frame(st);
+  const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
+  const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
+  int32_t* selected = selected_slot(a, st);
+  const long long nc = load_counts<R>(A, sweeps ? h : nullptr);
+  // a rescan is needed when the floor was raised and fewer than k sites
+  // reached it; every workgroup takes the same decision from the same counters
+  if (nc < a.k && raised) {
+    __syncthreads();
+    scan_sites<S, Q>(A, h, a.coarse, blockIdx.x, gridDim.x);
+    if (!last_block(&st->ticket)) return;
+    pick_floor_bin<R>(A, a.k, h, a.coarse, false);
+    if (threadIdx.x == 0) st->ticket = 0;
+    return;
+  }
+  if (!sweeps) return;
+  const Boundary bd = boundary_from(h, nc, a.k);
+  if (blockIdx.x == 0) store_boundary(bd, st);
+  sweep_chunk<S, Q>(A, a, blockIdx.x, cnt, bd, fr, selected, lds);
+}
+
+// Second launch: the exact resolution of the boundary bucket and the next
+// step's floor and frame, by one workgroup (a chain of dependent loads over
+// the list); after a rescan the append by all of them first.
+template <class S, int Q>
+__global__ __launch_bounds__(1024) void k_sel_tail(const StepArgs<typename StoreT<S>::R> A,
+                                                   const TailArgs a) {
+  using R = typename StoreT<S>::R;
+  SelState* st = A.sel;
+  __shared__ unsigned int h[kHistLds];
+  __shared__ SelScratch lds;
+  const int fallback = st->fallback;
+  Boundary bd{(long long)st->b_nc, st->b_bin, st->b_above};
+  unsigned long long sel_bnd = st->sel_bnd;
+  if (fallback) {
+    append_sites<S, Q>(A, blockIdx.x, gridDim.x);
+    if (!last_block(&st->ticket)) return;
+    if (threadIdx.x == 0) st->ticket = 0;
+    bd = boundary_from(h, load_counts<R>(A, h), a.k);
+    sel_bnd = sweep_all<S, Q>(A, a, bd, step_frame(st), selected_slot(a, st));
+    __threadfence();
+    __syncthreads();
+  } else if (blockIdx.x != 0) {
+    return;
+  }
+  tail_of<S, Q>(A, a, bd, sel_bnd, h, fallback != 0, lds);
+}
+
+// The whole selection of a small lattice by one workgroup.
+template <class S, int Q>
+__global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT<S>::R> A,
+                                                  const TailArgs a) {
+  using R = typename StoreT<S>::R;
+  SelState* st = A.sel;
+  __shared__ unsigned int h[kHistLds];
+  __shared__ SelScratch lds;
+  const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
+  const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
+  StepFrame fr = step_frame(st);
+  int32_t* selected = selected_slot(a, st);
+  long long nc = load_counts<R>(A, h);
+  if (nc < a.k && raised) {
+    __syncthreads();
+    scan_sites<S, Q>(A, h, a.coarse, 0, 1);
+    __threadfence();
+    __syncthreads();
+    pick_floor_bin<R>(A, a.k, h, a.coarse, false);
+    __threadfence();
+    __syncthreads();
+    append_sites<S, Q>(A, 0, 1);
+    __threadfence();
+    __syncthreads();
+    fr = step_frame(st);
+    nc = load_counts<R>(A, h);
+  }
+  const Boundary bd = boundary_from(h, nc, a.k);
+  const unsigned long long sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected);
+  __threadfence();
+  __syncthreads();
+  tail_of<S, Q>(A, a, bd, sel_bnd, h, true, lds);
 }
 
 // The MRT limiter (section 5) on an LBGK lattice: the step's selected sites,
 // which the sweep has just sent to f*, receive the MRT collision of their
 // pulled state instead (the source lattice is intact until the next step),
-// then the positivity rule when it is on.  The list is where k_fix_tail
+// then the positivity rule when it is on.  The list is where the tail
 // wrote it: the tape slot of the step when recording, else `selected`.
 template <class S, int Q>
 __global__ __launch_bounds__(256) void k_sel_mrt(const StepArgs<typename StoreT<S>::R> A,
@@ -876,21 +1065,19 @@ template <class S, int Q>
 static hipError_t launch_select_t(const SelectArgs& a, hipStream_t s) {
   using R = typename StoreT<S>::R;
   const StepArgs<R>& A = *(const StepArgs<R>*)a.step_args;
-  // All but the first workgroup of k_fb_scan, and all of k_fb_append,
-  // return at once unless this step rescans (rare).  k_fb_scan runs 64
-  // workgroups of 1024 threads: its first one reads the 4096-bucket
-  // histogram four words per thread (1.2 us per step less than 256 x 256).
-  hipLaunchKernelGGL((k_fb_scan<S, Q>), dim3(64), dim3(1024), 0, s, A, a.k, a.coarse, 0);
-  hipLaunchKernelGGL((k_fb_append<S, Q>), dim3(256), dim3(256), 0, s, A, a.k);
-  const long long nreg = (long long)A.tiles_x * A.tiles_y * 4;
-  const int gfix = (int)((nreg + kSweepRegions - 1) / kSweepRegions);
-  hipLaunchKernelGGL((k_fix_regions<S, Q>), dim3(gfix), dim3(kSweepRegions), 0, s, A, a.k, a.selected,
-                     a.segsel, a.blist, a.bcap, a.tape_sel, a.tape_len);
-  // the region sweep's stage: gfix workgroups x kSweepRegions regions x 64
-  // entries
-  hipLaunchKernelGGL((k_fix_tail<S, Q>), dim3(1), dim3(1024), 0, s, A, a.k, a.n_sites,
-                     a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel, a.tape_cnt,
-                     a.tape_len, (uint32_t*)a.segsel, (long long)gfix * kSweepRegions * 64);
+  const long long tiles = (long long)A.tiles_x * A.tiles_y;
+  const int nchunk = (int)((tiles * 4 + kSweepRegions - 1) / kSweepRegions);
+  const TailArgs t{a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
+                   a.tape_cnt, a.tape_len, a.segsel, a.coarse, nchunk};
+  if (nchunk == 1) {
+    hipLaunchKernelGGL((k_sel_one<S, Q>), dim3(1), dim3(1024), 0, s, A, t);
+  } else {
+    // one workgroup per chunk of regions; a rescan (rare) takes at least a
+    // workgroup per CU of a lattice that has the tiles for them
+    const int scan = (int)std::min<long long>((tiles + 3) / 4, 256);
+    hipLaunchKernelGGL((k_sel_sweep<S, Q>), dim3(std::max(nchunk, scan)), dim3(kSweepRegions), 0, s, A, t);
+    hipLaunchKernelGGL((k_sel_tail<S, Q>), dim3(scan), dim3(1024), 0, s, A, t);
+  }
   if (A.sel_mrt) {
     const long long g = (a.k + 255) / 256;
     hipLaunchKernelGGL((k_sel_mrt<S, Q>), dim3((unsigned)(g < 1 ? 1 : (g > 1024 ? 1024 : g))),
@@ -905,7 +1092,9 @@ static hipError_t launch_calibrate_t(const SelectArgs& a, hipStream_t s) {
   const StepArgs<R>& A = *(const StepArgs<R>*)a.step_args;
   // the floor is only ever raised when k is below a tenth of the lattice
   if (!(10 * a.k < a.n_sites && a.k > 0)) return hipSuccess;
-  hipLaunchKernelGGL((k_fb_scan<S, Q>), dim3(1024), dim3(256), 0, s, A, a.k, a.coarse, 1);
+  const long long tiles = (long long)A.tiles_x * A.tiles_y;
+  const int scan = (int)std::min<long long>((tiles + 3) / 4, 256);
+  hipLaunchKernelGGL((k_sel_calibrate<S, Q>), dim3(scan), dim3(1024), 0, s, A, a.k, a.coarse);
   return hipGetLastError();
 }
 
