@@ -9,67 +9,99 @@ __device__ __forceinline__ double rd(const void* p, long long i, int f64) {
   return f64 ? ((const double*)p)[i] : (double)((const float*)p)[i];
 }
 __device__ __forceinline__ void wr(void* p, long long i, double v, int f64) {
-  if (f64) ((double*)p)[i] = v;
-  else ((float*)p)[i] = (float)v;
+  if (f64) __builtin_nontemporal_store(v, (double*)p + i);
+  else __builtin_nontemporal_store((float)v, (float*)p + i);
+}
+
+// The site of a thread of the field kernels below: workgroups of 256 sites,
+// whole row segments where rows are long enough, 64 x 4 blocks otherwise, one
+// site per thread.  These kernels move each value once and are bound by HBM:
+// a site's loads all issue before its first store, without a division per
+// site (as grid-stride loops with
+// one they took 297 us to read a 4096^2 FP32 lattice out and 1829 us for 256^3
+// D3Q27, 195 and 622 us now).
+struct FieldGrid {
+  int nx, rows, tx, tiles_x;
+};
+inline FieldGrid field_grid(int nx, int rows) {
+  const int tx = nx >= 256 || rows == 1 ? 256 : 64;
+  return FieldGrid{nx, rows, tx, (nx + tx - 1) / tx};
+}
+inline unsigned field_blocks(const FieldGrid& g) {
+  const int ty = 256 / g.tx;
+  return (unsigned)g.tiles_x * (unsigned)((g.rows + ty - 1) / ty);
+}
+__device__ __forceinline__ bool field_site(const FieldGrid& g, int& x, int& y) {
+  const int t = (int)threadIdx.x;
+  x = (int)(blockIdx.x % (unsigned)g.tiles_x) * g.tx + t % g.tx;
+  y = (int)(blockIdx.x / (unsigned)g.tiles_x) * (256 / g.tx) + t / g.tx;
+  return (unsigned)x < (unsigned)g.nx && (unsigned)y < (unsigned)g.rows;
 }
 
 // f = f*(rho, u) of the configured kind (sections 6 and 8).
 template <class S, int Q>
-__global__ void k_set_eq(const void* rho, const void* ux, const void* uy, const void* uz, int in_f64, S* lat,
-                         long long qs, int nx, int ny, int pitch, int kind, double rho0) {
+__global__ __launch_bounds__(256) void k_set_eq(const void* rho, const void* ux, const void* uy,
+                                                const void* uz, int in_f64, S* lat, long long qs,
+                                                FieldGrid g, int pitch, int kind, double rho0) {
   using R = typename StoreT<S>::R;
   constexpr bool SH = StoreT<S>::shifted;
-  const long long n = (long long)nx * ny;
-  for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(s / nx), x = (int)(s % nx);
-    const R r = (R)rd<R>(rho, s, in_f64);
-    const R u = (R)rd<R>(ux, s, in_f64);
-    const R w = (Q >= 9 && uy) ? (R)rd<R>(uy, s, in_f64) : R(0);
-    R feq[Q];
-    if constexpr (Q == 27) {
-      const R wz = uz ? (R)rd<R>(uz, s, in_f64) : R(0);
-      equilibrium27<R, SH>(SH ? r - (R)rho0 : r, (R)rho0, u, w, wz, kind, feq);
-    } else {
-      equilibrium_v<R, Q, SH>(SH ? r - (R)rho0 : r, (R)rho0, u, w, kind, feq);
-    }
+  int x, y;
+  if (!field_site(g, x, y)) return;
+  const long long s = (long long)y * g.nx + x;
+  const long long o = (long long)y * pitch + x;
+  const R r = (R)rd<R>(rho, s, in_f64);
+  const R u = (R)rd<R>(ux, s, in_f64);
+  const R w = (Q >= 9 && uy) ? (R)rd<R>(uy, s, in_f64) : R(0);
+  R feq[Q];
+  if constexpr (Q == 27) {
+    const R wz = uz ? (R)rd<R>(uz, s, in_f64) : R(0);
+    equilibrium27<R, SH>(SH ? r - (R)rho0 : r, (R)rho0, u, w, wz, kind, feq);
+  } else {
+    equilibrium_v<R, Q, SH>(SH ? r - (R)rho0 : r, (R)rho0, u, w, kind, feq);
+  }
 #pragma unroll
-    for (int i = 0; i < Q; ++i) StoreT<S>::st(lat + (long long)i * qs + (long long)y * pitch + x, feq[i]);
+  for (int i = 0; i < Q; ++i) StoreT<S>::st(lat + (long long)i * qs + o, feq[i]);
+}
+
+template <class S, int Q>
+__global__ __launch_bounds__(256) void k_set_pop(const void* f, int in_f64, S* lat, long long qs,
+                                                 FieldGrid g, int pitch, double rho0) {
+  constexpr bool SH = StoreT<S>::shifted;
+  int x, y;
+  if (!field_site(g, x, y)) return;
+  const long long n = (long long)g.nx * g.rows, s = (long long)y * g.nx + x;
+  const long long o = (long long)y * pitch + x;
+  double v[Q];
+  if (in_f64) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = __builtin_nontemporal_load((const double*)f + (long long)i * n + s);
+  } else {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = (double)__builtin_nontemporal_load((const float*)f + (long long)i * n + s);
+  }
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    if (SH) v[i] -= wt<double, Q>(i) * rho0;
+    StoreT<S>::st(lat + (long long)i * qs + o, (typename StoreT<S>::R)v[i]);
   }
 }
 
 template <class S, int Q>
-__global__ void k_set_pop(const void* f, int in_f64, S* lat, long long qs, int nx, int ny,
-                          int pitch, double rho0) {
+__global__ __launch_bounds__(256) void k_get_pop(void* f, int out_f64, const S* lat, long long qs,
+                                                 FieldGrid g, int pitch, double rho0) {
   constexpr bool SH = StoreT<S>::shifted;
-  const long long n = (long long)nx * ny;
-  for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(s / nx), x = (int)(s % nx);
+  int x, y;
+  if (!field_site(g, x, y)) return;
+  const long long n = (long long)g.nx * g.rows, s = (long long)y * g.nx + x;
+  const long long o = (long long)y * pitch + x;
+  typename StoreT<S>::R raw[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      double v = rd<double>(f, (long long)i * n + s, in_f64);
-      if (SH) v -= wt<double, Q>(i) * rho0;
-      StoreT<S>::st(lat + (long long)i * qs + (long long)y * pitch + x,
-                    (typename StoreT<S>::R)v);
-    }
-  }
-}
-
-template <class S, int Q>
-__global__ void k_get_pop(void* f, int out_f64, const S* lat, long long qs, int nx, int ny,
-                          int pitch, double rho0) {
-  constexpr bool SH = StoreT<S>::shifted;
-  const long long n = (long long)nx * ny;
-  for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(s / nx), x = (int)(s % nx);
+  for (int i = 0; i < Q; ++i) raw[i] = StoreT<S>::ld(lat + (long long)i * qs + o);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      double v = (double)StoreT<S>::ld(lat + (long long)i * qs + (long long)y * pitch + x);
-      if (SH) v += wt<double, Q>(i) * rho0;
-      wr(f, (long long)i * n + s, v, out_f64);
-    }
+  for (int i = 0; i < Q; ++i) {
+    double v = (double)raw[i];
+    if (SH) v += wt<double, Q>(i) * rho0;
+    wr(f, (long long)i * n + s, v, out_f64);
   }
 }
 
@@ -93,18 +125,17 @@ __device__ __forceinline__ void site_moments64(const S* lat, long long qs, int p
 }
 
 template <class S, int Q>
-__global__ void k_moments(const S* lat, long long qs, int nx, int ny, int pitch, double rho0,
-                          void* rho, void* ux, void* uy, int out_f64) {
-  const long long n = (long long)nx * ny;
-  for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(s / nx), x = (int)(s % nx);
-    double f[Q], r, jx, jy;
-    site_moments64<S, Q>(lat, qs, pitch, x, y, rho0, f, r, jx, jy);
-    wr(rho, s, r, out_f64);
-    wr(ux, s, jx / r, out_f64);
-    if (uy) wr(uy, s, jy / r, out_f64);
-  }
+__global__ __launch_bounds__(256) void k_moments(const S* lat, long long qs, FieldGrid g, int pitch,
+                                                 double rho0, void* rho, void* ux, void* uy,
+                                                 int out_f64) {
+  int x, y;
+  if (!field_site(g, x, y)) return;
+  const long long s = (long long)y * g.nx + x;
+  double f[Q], r, jx, jy;
+  site_moments64<S, Q>(lat, qs, pitch, x, y, rho0, f, r, jx, jy);
+  wr(rho, s, r, out_f64);
+  wr(ux, s, jx / r, out_f64);
+  if (uy) wr(uy, s, jy / r, out_f64);
 }
 
 // Per-block partial sums in a fixed order (deterministic), then one block
@@ -213,11 +244,6 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats_final(const double* par
 }
 
 // ---------------------------------------------------------------------------
-static inline int grid_for(long long n) {
-  long long g = (n + 255) / 256;
-  return (int)(g < 4096 ? (g < 1 ? 1 : g) : 4096);
-}
-
 #define LBM_QSWITCH(Q, ...)                                                              \
   if (Q == 27) { constexpr int QQ = 27; __VA_ARGS__; }                                   \
   else if (Q == 9) { constexpr int QQ = 9; __VA_ARGS__; }                                \
@@ -233,30 +259,30 @@ static inline int grid_for(long long n) {
 hipError_t launch_set_eq(int storage, int Q, const void* rho, const void* ux, const void* uy,
                          const void* uz, int in_f64, void* lat, long long qs, int nx, int ny, int pitch,
                          int eq_kind, double rho0, hipStream_t s) {
-  const int g = grid_for((long long)nx * ny);
-  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_set_eq<S, QQ>), dim3(g), dim3(256), 0, s, rho, ux, uy, uz, in_f64, (S*)lat, qs, nx, ny, pitch, eq_kind, rho0));
+  const FieldGrid g = field_grid(nx, ny);
+  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_set_eq<S, QQ>), dim3(field_blocks(g)), dim3(256), 0, s, rho, ux, uy, uz, in_f64, (S*)lat, qs, g, pitch, eq_kind, rho0));
   return hipGetLastError();
 }
 
 hipError_t launch_set_pop(int storage, int Q, const void* f, int in_f64, void* lat, long long qs,
                           int nx, int ny, int pitch, double rho0, hipStream_t s) {
-  const int g = grid_for((long long)nx * ny);
-  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_set_pop<S, QQ>), dim3(g), dim3(256), 0, s, f, in_f64, (S*)lat, qs, nx, ny, pitch, rho0));
+  const FieldGrid g = field_grid(nx, ny);
+  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_set_pop<S, QQ>), dim3(field_blocks(g)), dim3(256), 0, s, f, in_f64, (S*)lat, qs, g, pitch, rho0));
   return hipGetLastError();
 }
 
 hipError_t launch_get_pop(int storage, int Q, void* f, int out_f64, const void* lat, long long qs,
                           int nx, int ny, int pitch, double rho0, hipStream_t s) {
-  const int g = grid_for((long long)nx * ny);
-  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_get_pop<S, QQ>), dim3(g), dim3(256), 0, s, f, out_f64, (const S*)lat, qs, nx, ny, pitch, rho0));
+  const FieldGrid g = field_grid(nx, ny);
+  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_get_pop<S, QQ>), dim3(field_blocks(g)), dim3(256), 0, s, f, out_f64, (const S*)lat, qs, g, pitch, rho0));
   return hipGetLastError();
 }
 
 hipError_t launch_moments(int storage, int Q, const void* lat, long long qs, int nx, int ny,
                           int pitch, double rho0, void* rho, void* ux, void* uy, int out_f64,
                           hipStream_t s) {
-  const int g = grid_for((long long)nx * ny);
-  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_moments<S, QQ>), dim3(g), dim3(256), 0, s, (const S*)lat, qs, nx, ny, pitch, rho0, rho, ux, uy, out_f64));
+  const FieldGrid g = field_grid(nx, ny);
+  LBM_DISPATCH(storage, Q, hipLaunchKernelGGL((k_moments<S, QQ>), dim3(field_blocks(g)), dim3(256), 0, s, (const S*)lat, qs, g, pitch, rho0, rho, ux, uy, out_f64));
   return hipGetLastError();
 }
 
