@@ -601,6 +601,23 @@ static hipError_t check_now(lbm_ctx* c) {
                       c->steps, c->stream);
 }
 
+// Lattices whose steps run many to a launch (lbm_small.hip).
+static bool takes_small(const lbm_ctx* c) {
+  return c->L.Q == 3 && c->cfg.nx <= kSmallSites && c->cfg.collision == LBM_LBGK &&
+         !(c->cfg.limiters & LBM_LIM_MEDIAN) && c->cfg.ens_limiter == LBM_ENS_NONE &&
+         !c->cfg.nl_filter && !c->L.adj.on;
+}
+
+static hipError_t small_steps(lbm_ctx* c, long long n) {
+  const void* args;
+  if (c->f64()) { c->a64.src = c->a64.dst = c->lat(c->cur); args = &c->a64; }
+  else { c->a32.src = c->a32.dst = c->lat(c->cur); args = &c->a32; }
+  const SmallArgs a{n, c->L.k, c->L.n_sites, (int32_t*)(c->ws + c->L.off_selected), 0ull};
+  const hipError_t e = launch_small(c->cfg.storage, args, a, c->stream);
+  if (e == hipSuccess) c->steps += n;
+  return e;
+}
+
 static lbm_status run_steps(lbm_ctx* c, long long n, hipEvent_t* ev) {
   // Launch-bound lattices gain most: whole groups of kGraphSteps steps
   // replay a captured graph (not with events, which time each step).  The
@@ -612,7 +629,21 @@ static lbm_status run_steps(lbm_ctx* c, long long n, hipEvent_t* ev) {
   const bool graphs = !ev && (rec || !c->L.adj.on);
   const long long ci = c->cfg.check_interval;
   long long eager = 0;   // eager steps of this call (index into ev)
+  const bool small = !ev && takes_small(c);
   while (n > 0) {
+    if (small) {
+      // up to the next divergence check; a launch stays within milliseconds
+      long long m = std::min<long long>(n, 1024);
+      if (ci > 0) m = std::min(m, ci - c->steps % ci);
+      hipError_t e = small_steps(c, m);
+      if (e != hipSuccess) return hip_fail(e, "lbm_step");
+      n -= m;
+      if (ci > 0 && c->steps % ci == 0) {
+        e = check_now(c);
+        if (e != hipSuccess) return hip_fail(e, "check");
+      }
+      continue;
+    }
     bool fits = graphs && n >= kGraphSteps;
     if (fits && rec) {
       const long long K = c->L.adj.K;

@@ -39,7 +39,8 @@ enum ElbmBranch : int { EB_ROOT = 0, EB_CUTOFF = 1, EB_NOROOT = 2, EB_NONPOS = 3
 // loaded and stored nontemporally: a step reads and writes each one once,
 // and the two lattices are far larger than the caches (measured 5 % faster
 // steps at 4096^2 than with cached loads).  ldc is the cached load, for the
-// kernels that read a population again (halos staged in LDS).
+// kernels that read a population again (halos staged in LDS); pack is the
+// rounding to the storage form.
 // ---------------------------------------------------------------------------
 struct bf16_t { uint16_t bits; };
 
@@ -51,6 +52,7 @@ template <> struct StoreT<double> {
   static __device__ __forceinline__ double raw(const double* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ double ld(const double* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ double ldc(const double* p) { return *p; }
+  static __device__ __forceinline__ double pack(double v) { return v; }
   static __device__ __forceinline__ void st(double* p, double v) { __builtin_nontemporal_store(v, p); }
 };
 template <> struct StoreT<float> {
@@ -60,6 +62,7 @@ template <> struct StoreT<float> {
   static __device__ __forceinline__ float raw(const float* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ float ld(const float* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ float ldc(const float* p) { return *p; }
+  static __device__ __forceinline__ float pack(float v) { return v; }
   static __device__ __forceinline__ void st(float* p, float v) { __builtin_nontemporal_store(v, p); }
 };
 template <> struct StoreT<_Float16> {
@@ -69,6 +72,7 @@ template <> struct StoreT<_Float16> {
   static __device__ __forceinline__ _Float16 raw(const _Float16* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ float ld(const _Float16* p) { return (float)__builtin_nontemporal_load(p); }
   static __device__ __forceinline__ float ldc(const _Float16* p) { return (float)*p; }
+  static __device__ __forceinline__ _Float16 pack(float v) { return (_Float16)v; }
   static __device__ __forceinline__ void st(_Float16* p, float v) { __builtin_nontemporal_store((_Float16)v, p); }
 };
 template <> struct StoreT<bf16_t> {
@@ -86,10 +90,15 @@ template <> struct StoreT<bf16_t> {
   static __device__ __forceinline__ float ldc(const bf16_t* p) {
     return __uint_as_float(((uint32_t)p->bits) << 16);
   }
-  static __device__ __forceinline__ void st(bf16_t* p, float v) {
+  static __device__ __forceinline__ bf16_t pack(float v) {
     // gfx950's conversion instruction: round to nearest even, NaN stays NaN
-    const uint16_t r = __builtin_bit_cast(uint16_t, (__bf16)v);
-    __builtin_nontemporal_store(r, &p->bits);
+    bf16_t r;
+    r.bits = __builtin_bit_cast(uint16_t, (__bf16)v);
+    return r;
+  }
+  static __device__ __forceinline__ void st(bf16_t* p, float v) {
+    const bf16_t r = pack(v);
+    __builtin_nontemporal_store(r.bits, &p->bits);
   }
 };
 

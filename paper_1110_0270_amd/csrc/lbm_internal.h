@@ -232,5 +232,15 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_select_calibrate(const SelectArgs& a, hipStream_t s);
 void init_select_state(SelState* h, int f64);
 
+// Many steps of a short D1Q3 LBGK lattice in one launch, from A.src into
+// A.dst (which may be the same lattice).
+constexpr int kSmallSites = 4096;
+struct SmallArgs {
+  long long steps, k, n_sites;
+  int32_t* selected;          // out: the last step's selected sites
+  unsigned long long quarter; // set by launch_small
+};
+hipError_t launch_small(int storage, const void* step_args, SmallArgs a, hipStream_t s);
+
 
 }  // namespace lbm
