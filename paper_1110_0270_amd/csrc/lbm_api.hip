@@ -313,7 +313,8 @@ void fill_args(StepArgs<R>& A, const lbm_config* c, const Layout& L, char* ws) {
 
 }  // namespace
 
-// Steps per captured graph (even: a replay starts and ends on the same lattice).
+// Steps per captured graph: an even number of launches of one, two or four
+// steps (a replay starts and ends on the same lattice).
 constexpr int kGraphSteps = 16;
 
 struct lbm_ctx {
@@ -552,6 +553,28 @@ static SelectArgs select_args(lbm_ctx* c, const void* args) {
     return sa;
 }
 
+// Steps that one launch of launch_multi takes for this context (0: none).
+static int multi_of(const lbm_ctx* c) {
+  const lbm_config& g = c->cfg;
+  if (c->L.Q != 9 || (g.limiters & LBM_LIM_EHRENFEST) || g.ens_limiter != LBM_ENS_NONE || g.nl_filter)
+    return 0;
+  return multi_steps(g.storage, g.collision, (g.limiters & LBM_LIM_MEDIAN) != 0, g.nx, g.ny);
+}
+
+static hipError_t multi_step(lbm_ctx* c, int m) {
+  const void* args;
+  const int src = c->cur, dst = 1 - c->cur;
+  if (c->f64()) { c->a64.src = c->lat(src); c->a64.dst = c->lat(dst); args = &c->a64; }
+  else { c->a32.src = c->lat(src); c->a32.dst = c->lat(dst); args = &c->a32; }
+  const hipError_t e = launch_multi(c->cfg.storage, c->cfg.collision,
+                                    (c->cfg.limiters & LBM_LIM_MEDIAN) != 0, args, c->cfg.nx,
+                                    c->cfg.ny, c->stream);
+  if (e != hipSuccess) return e;
+  c->cur = dst;
+  c->steps += m;
+  return hipSuccess;
+}
+
 // Capture kGraphSteps steps from lattice c->cur on the library's own stream
 // (the caller's may be the legacy default stream, which cannot be
 // captured); the host-side step state is restored afterwards.
@@ -566,7 +589,9 @@ static hipError_t capture_graph(lbm_ctx* c) {
   hipGraph_t g = nullptr;
   e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    for (int s = 0; s < kGraphSteps && e == hipSuccess; ++s) e = one_step(c);
+    const int m = multi_of(c);
+    for (int s = 0; s < kGraphSteps && e == hipSuccess; s += m ? m : 1)
+      e = m ? multi_step(c, m) : one_step(c);
     const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &g);
     if (e == hipSuccess) e = e2;
   }
@@ -644,16 +669,26 @@ static lbm_status run_steps(lbm_ctx* c, long long n, hipEvent_t* ev) {
       }
       continue;
     }
-    bool fits = graphs && n >= kGraphSteps;
-    if (fits && rec) {
-      const long long K = c->L.adj.K;
-      fits = c->steps + kGraphSteps <= c->cfg.max_steps && K - c->steps % K >= kGraphSteps;
-    }
-    if (fits && ci > 0) fits = ci - c->steps % ci >= kGraphSteps;
-    if (fits) {
-      const lbm_status st = replay_graph(c);
-      if (st != LBM_OK) return st;
-      n -= kGraphSteps;
+    // q steps that cross neither a checkpoint nor the end of the tape nor a
+    // divergence check
+    auto fits = [&](long long q) {
+      if (!graphs || n < q) return false;
+      if (rec && !(c->steps + q <= c->cfg.max_steps && c->L.adj.K - c->steps % c->L.adj.K >= q))
+        return false;
+      return ci <= 0 || ci - c->steps % ci >= q;
+    };
+    const int m = multi_of(c);
+    const bool replay = fits(kGraphSteps);
+    if (replay || (m > 0 && fits(m))) {
+      const long long q = replay ? kGraphSteps : m;
+      if (replay) {
+        const lbm_status st = replay_graph(c);
+        if (st != LBM_OK) return st;
+      } else {
+        const hipError_t e = multi_step(c, m);
+        if (e != hipSuccess) return hip_fail(e, "lbm_step");
+      }
+      n -= q;
       if (rec) {
         const hipError_t e = adjoint_after_step(c->L.adj, c->ws, c->steps, c->lat(c->cur),
                                                 c->L.lat_bytes, c->stream);

@@ -232,6 +232,13 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 hipError_t launch_select_calibrate(const SelectArgs& a, hipStream_t s);
 void init_select_state(SelState* h, int f64);
 
+// Several steps of a D2Q9 lattice without the Ehrenfest selection in one
+// launch, A.src -> A.dst: how many a launch takes (1, 2 or 4; 0: the lattice
+// is left to the step kernel), and the launch.
+int multi_steps(int storage, int coll, bool median, int nx, int ny);
+hipError_t launch_multi(int storage, int coll, bool median, const void* step_args, int nx, int ny,
+                        hipStream_t s);
+
 // Many steps of a short D1Q3 LBGK lattice in one launch, from A.src into
 // A.dst (which may be the same lattice).
 constexpr int kSmallSites = 4096;

@@ -15,21 +15,9 @@
 #include <hip/hip_ext.h>
 
 #include "lbm_collide.h"
+#include "lbm_median.h"
 
 namespace lbm {
-
-template <class R>
-__device__ __forceinline__ void sort_net9(R a[9]) {
-#pragma unroll
-  for (int pass = 0; pass < 9; ++pass) {
-#pragma unroll
-    for (int j = pass & 1; j + 1 < 9; j += 2) {
-      const R lo = fmin(a[j], a[j + 1]), hi = fmax(a[j], a[j + 1]);
-      a[j] = lo;
-      a[j + 1] = hi;
-    }
-  }
-}
 
 // Sites of an FP32 ELBM step that need the FP64 root solve, listed by the
 // step kernel (alpha_max < f64_below: near the no-root branch, where
@@ -271,29 +259,22 @@ void k_step(const StepArgs<typename StoreT<S>::R> A) {
         // wavefronts without a site above delta skip the neighbourhood's sort
         R med = R(0);
         if (__ballot(cand)) {
-          R nb[9];
-          int n = 0;
-          constexpr int NN = (Q == 9) ? 9 : 3;
-#pragma unroll
-          for (int k = 0; k < NN; ++k) {
-            const int dy = (Q == 9) ? k / 3 - 1 : 0, dx = (Q == 9) ? k % 3 - 1 : k - 1;
-            const R val = sdS[(by + HY + dy) * SW + lx + 1 + dx];
-            const bool in = !(val != val);
-            n += in ? 1 : 0;
-            nb[k] = in ? val : r_inf<R>();
-          }
+          auto at_nb = [&](int dy, int dx) { return sdS[(by + HY + dy) * SW + lx + 1 + dx]; };
           if constexpr (Q == 9) {
-            sort_net9<R>(nb);
-            const int rank = (n + 1) / 2 - 1;
-            med = nb[0];
-#pragma unroll
-            for (int k = 1; k < 9; ++k) med = rank == k ? nb[k] : med;
+            med = median_of_9<R>([&](int k) { return at_nb(k / 3 - 1, k % 3 - 1); });
           } else {
+            R nb[3];
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const R val = at_nb(0, k - 1);
+              const bool in = !(val != val);
+              n += in ? 1 : 0;
+              nb[k] = in ? val : r_inf<R>();
+            }
             R a0 = fmin(nb[0], nb[1]), a1 = fmax(nb[0], nb[1]);
-            const R a2 = fmax(a1, nb[2]);
             a1 = fmin(a1, nb[2]);
             const R b0 = fmin(a0, a1), b1 = fmax(a0, a1);
-            (void)a2;
             med = ((n + 1) / 2 - 1) == 0 ? b0 : b1;
           }
         }
