@@ -40,6 +40,7 @@ struct Layout {
   size_t lat_bytes = 0;
   int rows = 0;            // ny, or nz * ny for D3Q27
   size_t off_nl = 0;       // nonlocal filter coefficients (27 values of the compute type)
+  size_t off_med3 = 0, med3_bytes = 0;  // D3Q27 median step: Med3State and the chunk records
   size_t off_lat[2] = {0, 0}, off_omega = 0, off_sel = 0, off_cnt = 0, off_partial = 0,
          off_stats = 0, off_div = 0, off_ckey = 0, off_cidx = 0, off_cmom = 0, off_hist = 0,
          off_coarse = 0, off_wcount = 0, off_ccount = 0, off_stage = 0, off_blist = 0,
@@ -160,6 +161,10 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
   L.off_cnt = take((size_t)kCntSlots * CNT_N * sizeof(unsigned long long));
   L.off_partial = take(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
   L.off_nl = c->nl_filter ? take(27 * rb) : 0;
+  if (L.Q == 27 && (c->limiters & LBM_LIM_MEDIAN)) {
+    L.med3_bytes = sizeof(Med3State) + (size_t)med3_chunks(c->storage, c->nx, c->ny, c->nz) * sizeof(Med3Chunk);
+    L.off_med3 = take(L.med3_bytes);
+  }
   L.off_stats = take(8 * sizeof(double));
   L.off_div = take(sizeof(long long));
   if (c->limiters & LBM_LIM_EHRENFEST) {
@@ -208,6 +213,7 @@ void fill_args(StepArgs<R>& A, const lbm_config* c, const Layout& L, char* ws) {
   A.ny3 = c->ny;
   A.nz = c->lattice == LBM_D3Q27 ? c->nz : 1;
   A.nl_coef = L.off_nl ? (const R*)(ws + L.off_nl) : nullptr;
+  A.med3 = L.off_med3 ? (Med3State*)(ws + L.off_med3) : nullptr;
   const TileShape ts = tile_shape(L.Q, (c->limiters & LBM_LIM_MEDIAN) != 0, c->nx);
   A.tiles_x = (c->nx + ts.tx - 1) / ts.tx;
   A.tiles_y = (c->ny + ts.ty - 1) / ts.ty;
@@ -395,6 +401,7 @@ lbm_status lbm_init(const lbm_config* cfg, void* ws, size_t ws_bytes, void* stre
   }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->ws + L.off_cnt, 0, (size_t)kCntSlots * CNT_N * 8, c->stream);
+  if (e == hipSuccess && L.off_med3) e = hipMemsetAsync(c->ws + L.off_med3, 0, L.med3_bytes, c->stream);
   if (e == hipSuccess && L.off_ens) e = hipMemsetAsync(c->ws + L.off_ens, 0, sizeof(EnsState), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->ws + L.off_div, 0xff, sizeof(long long), c->stream);
   if (e == hipSuccess && L.off_f64cnt)

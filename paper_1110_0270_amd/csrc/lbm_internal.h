@@ -93,6 +93,20 @@ struct EnsState {
 };
 constexpr int kEnsSlots = 64;
 
+// Device state of the D3Q27 median step, followed by one record per chunk of
+// the lattice (lbm_step3.hip): all zero between steps but for `dense`.
+struct Med3State {
+  unsigned long long tally;  // second kernel: workgroups done, and (high half) chunks with a candidate
+  int dense;                 // the next step goes to the second kernel alone
+  int pad[5];
+};
+struct Med3Chunk {
+  unsigned long long flag;        // the first kernel found a site that may lie above delta
+  unsigned long long pos_events;  // its positivity events (void if the chunk is taken again)
+};
+__host__ __device__ inline Med3Chunk* med3_chunk(Med3State* m) { return reinterpret_cast<Med3Chunk*>(m + 1); }
+long long med3_chunks(int storage, int nx, int ny, int nz);
+
 template <class R> struct KeyOf;
 template <> struct KeyOf<float> { using T = uint32_t; };
 template <> struct KeyOf<double> { using T = unsigned long long; };
@@ -164,6 +178,8 @@ struct StepArgs {
   // general nonlocal filter of section 4: the coefficients d(y) in tensor
   // order of the shifts y ([3] D1Q3, [9] D2Q9), or nullptr
   const R* nl_coef;
+  // D3Q27 median step: its state and chunk records, or nullptr
+  Med3State* med3;
 };
 
 // Launchers (one per translation unit); return hipSuccess or the error.

@@ -79,4 +79,40 @@ __device__ __forceinline__ void equilibrium27(R m0, R rho0, R ux, R uy, R uz, in
   }
 }
 
+// False where the upper bound of site_dS_dev's screening proves Delta S below
+// `screen` (see there); true elsewhere, and everywhere for screen <= 0.  The
+// bound alone: without the exact sum the kernel keeps 27 registers fewer.
+template <class R, bool SH>
+__device__ __forceinline__ bool may_exceed27(const R v[27], const R feq[27], R m0, R rho0, R ux, R uy,
+                                             R uz, int kind, R screen) {
+  if (!(screen > R(0))) return true;
+  R dx[3], dy[3], dz[3];
+  eq_dev6<R>(ux, kind, dx);
+  eq_dev6<R>(uy, kind, dy);
+  eq_dev6<R>(uz, kind, dz);
+  const R rho = SH ? rho0 + m0 : m0;
+  const R irs = R(216) * rcp<R>(rho);
+  R rx[3], ry[3], rz[3];
+  bool bad = rho <= R(0);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const R fx = (R)c1(a - 1) + dx[a], fy = (R)c1(a - 1) + dy[a], fz = (R)c1(a - 1) + dz[a];
+    rx[a] = irs * rcp<R>(fx);
+    ry[a] = rcp<R>(fy);
+    rz[a] = rcp<R>(fz);
+    bad |= (fx <= R(0)) | (fy <= R(0)) | (fz <= R(0));
+  }
+  R sdy = R(0), ymax = R(0);
+#pragma unroll
+  for (int i = 0; i < 27; ++i) {
+    const R d = feq[i] - v[i];
+    const R y = d * (rx[vx_of<27>(i) + 1] * ry[vy_of<27>(i) + 1] * rz[vz_of<27>(i) + 1]);
+    ymax = fmax(ymax, y);
+    sdy += d * y;
+  }
+  const R ub = sdy * (R(0.5) + ymax * R(1.0 / 3.0));
+  // (a NaN compares false and so may exceed)
+  return bad || !(ymax <= R(0.5) && ub * R(1.0001) < screen);
+}
+
 }  // namespace lbm

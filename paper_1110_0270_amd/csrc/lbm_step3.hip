@@ -6,10 +6,20 @@
 //   -> LBGK collision (eq. CollisionIntegral) -> positivity rule (section 4)
 //   -> store into the second lattice.
 // Without the median filter every lane takes one site of a 256-site row
-// segment.  With it, a workgroup takes a TX x TY column of sites and marches
-// along z through ZC layers, keeping Delta S of three layers (the tile plus
-// a one-site halo) in an LDS ring: each layer's Delta S is evaluated once
-// per column, not once per neighbour.
+// segment (k_step3).  With it two kernels share the step:
+//   k_step3 takes the whole lattice as if no site were filtered, screens each
+//   site's Delta S against delta by a bound and flags the chunk (64 x 8 columns
+//   of up to 32 layers) of every site not proved below it;
+//   k_step3_median takes the flagged chunks again with the filter: a workgroup
+//   marches along z through a chunk's layers, keeping Delta S of three layers
+//   (the tile plus a one-site halo) in an LDS ring, so that each layer's
+//   Delta S is evaluated once per column, not once per neighbour.
+// Where most chunks hold such a site (delta = 0) the first kernel would be
+// waste: a step that finds more than a quarter of the chunks flagged leaves
+// the next one to k_step3_median alone, until fewer than an eighth hold a
+// candidate (Med3State; the result does not depend on it).  The first kernel's
+// empty launch then costs 17 us (256^3, 1163 -> 1215 us a step at delta = 0,
+// against 1105 -> 665 at delta = 1e-3 in the Taylor-Green vortex).
 #include <hip/hip_ext.h>
 
 #include "lbm_collide.h"
@@ -26,7 +36,7 @@ __device__ __forceinline__ int wrap_mod(int g, int n) {
   return (r < 0 || r >= n) ? ((g % n) + n) % n : r;
 }
 
-// After the filter: LBGK, the positivity rule, the store.
+// After the filter: LBGK, the positivity rule (its events to cnt), the store.
 template <class S>
 __device__ __forceinline__ void finish27(const StepArgs<typename StoreT<S>::R>& A, unsigned off,
                                          bool valid, typename StoreT<S>::R v[27],
@@ -45,25 +55,45 @@ __device__ __forceinline__ void finish27(const StepArgs<typename StoreT<S>::R>& 
 #pragma unroll
     for (int i = 0; i < 27; ++i) StoreT<S>::st(at(dst + (long long)i * A.qs, off), v[i]);
   }
-  if (A.positivity && A.count_events) count_event(pos_event, cnt + CNT_POSITIVITY);
+  if (A.positivity && A.count_events) count_event(pos_event, cnt);
 }
 
-template <class S>
+constexpr int kM3X = 64, kM3Y = 8;
+// Layers of a chunk: 1.06 layers of Delta S per layer (FP32)
+template <class S> constexpr int m3_layers() { return sizeof(typename StoreT<S>::R) == 4 ? 32 : 16; }
+
+// MED: the first of the median step's two kernels.  Bound by HBM: with the
+// marching kernel alone every site's Delta S, its halo's and a second pull of
+// its own took 1105 us at 256^3 FP32 (delta = 1e-3, no site above it); now
+// 650 us (5.6 TB/s).  One segment per workgroup: a loop over four kept 25
+// registers more (717 us).
+template <class S, bool MED>
 __global__ __launch_bounds__(256) void k_step3(const StepArgs<typename StoreT<S>::R> A) {
   using R = typename StoreT<S>::R;
   constexpr bool SH = StoreT<S>::shifted;
-  // workgroup -> (256-site segment of a row, row z * ny + y)
+  if (MED && A.med3->dense) return;
+  // workgroup -> (256-site segment of a row, row z * ny3 + y)
   const int segs = (A.nx + 255) / 256;
   const int row = (int)blockIdx.x / segs, x = ((int)blockIdx.x % segs) * 256 + (int)threadIdx.x;
   const int y = row % A.ny3, z = row / A.ny3;
   const bool valid = x < A.nx;
-  unsigned long long* const cnt = A.counters + (blockIdx.x % kCntSlots) * CNT_N;
   R v[27], feq[27];
+  bool may = false;
   if (valid) {
     R m0, ux, uy, uz;
     pull27<S>((const S*)A.src, A.qs, A.pitch, A.nx, A.ny3, A.nz, x, y, z, v);
     moments27<R, SH>(v, A.rho0, m0, ux, uy, uz);
     equilibrium27<R, SH>(m0, A.rho0, ux, uy, uz, A.eq_kind, feq);
+    if constexpr (MED) may = may_exceed27<R, SH>(v, feq, m0, A.rho0, ux, uy, uz, A.eq_kind, A.med_delta);
+  }
+  unsigned long long* cnt = A.counters + (blockIdx.x % kCntSlots) * CNT_N + CNT_POSITIVITY;
+  if constexpr (MED) {
+    // a wavefront's 64 sites of a row lie in one chunk
+    const int tx = (A.nx + kM3X - 1) / kM3X, ty = (A.ny3 + kM3Y - 1) / kM3Y;
+    Med3Chunk* chunk = med3_chunk(A.med3) + (z / m3_layers<S>() * ty + y / kM3Y) * tx + x / kM3X;
+    cnt = &chunk->pos_events;
+    const unsigned long long any = __ballot(may);
+    if (any && (int)__lane_id() == __ffsll((long long)any) - 1) chunk->flag = 1ull;
   }
   finish27<S>(A, (unsigned)(row * A.pitch + x), valid, v, feq, cnt);
 }
@@ -117,6 +147,34 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
   const bool valid = x < A.nx && y < A.ny3;
   unsigned long long* const cnt = A.counters + (b % kCntSlots) * CNT_N;
 
+  // every workgroup reads the mode before it takes its ticket, so the last
+  // one may change it
+  const bool dense = A.med3->dense != 0;
+  const bool flagged = med3_chunk(A.med3)[tb].flag != 0;
+  // one 64-bit atomic: workgroups done (low half), chunks with a candidate (high)
+  auto leave = [&](bool had) {
+    if (tid != 0) return;
+    // the first kernel's positivity events stand where this one did nothing
+    Med3Chunk* const chunk_st = med3_chunk(A.med3) + tb;
+    const unsigned long long pos = chunk_st->pos_events;
+    if (pos && !dense && !flagged) atomicAdd(cnt + CNT_POSITIVITY, pos);
+    if (pos) chunk_st->pos_events = 0ull;
+    if (flagged) chunk_st->flag = 0ull;
+    const unsigned long long mine = 1ull | ((had ? 1ull : 0ull) << 32);
+    const unsigned long long all = atomicAdd(&A.med3->tally, mine) + mine;
+    if ((unsigned int)all == (unsigned int)T) {
+      const unsigned long long held = all >> 32;
+      A.med3->dense = dense ? (8 * held >= (unsigned long long)T ? 1 : 0)
+                            : (4 * held > (unsigned long long)T ? 1 : 0);
+      A.med3->tally = 0ull;
+    }
+  };
+  if (!dense && !flagged) {
+    leave(false);
+    return;
+  }
+  bool had = false;      // a candidate in this chunk
+
   // Delta S of layer z (periodic) over the tile and its halo into ring slot
   // `slot`; positions beyond the lattice wrap, so ragged tiles need no
   // special case.
@@ -147,6 +205,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     // the count, and only wavefronts with an accepted site select the 14th.
     const R dS = valid ? ring[sc][(ly + 1) * SW + lx + 1] : R(0);
     const bool cand = valid && (dS > A.med_delta) && (dS < r_inf<R>());
+    had |= __ballot(cand) != 0ull;
     bool acc = false;
     R med = R(0);
     auto nbr = [&](int k) {
@@ -179,9 +238,10 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
       for (int i = 0; i < 27; ++i) v[i] = feq[i] + c * (v[i] - feq[i]);
     }
     if (A.count_events) count_event(acc, cnt + CNT_MEDIAN);
-    finish27<S>(A, (unsigned)((z * A.ny3 + y) * A.pitch + x), valid, v, feq, cnt);
+    finish27<S>(A, (unsigned)((z * A.ny3 + y) * A.pitch + x), valid, v, feq, cnt + CNT_POSITIVITY);
     __syncthreads();   // the next layer overwrites the ring slot of z - 1
   }
+  leave(__syncthreads_or(had));
 }
 
 // ---------------------------------------------------------------------------
@@ -190,21 +250,30 @@ static hipError_t launch3(bool median, const void* args, hipStream_t s, hipEvent
                           hipEvent_t e1) {
   using R = typename StoreT<S>::R;
   const StepArgs<R>& A = *(const StepArgs<R>*)args;
+  const dim3 rows((unsigned)((A.nx + 255) / 256 * (long long)A.ny3 * A.nz));
   if (median) {
-    // 64 x 8 columns of 32 layers: 1.29 halo sites per site, 1.06 layers
-    // per layer (FP32 arithmetic: 64 x 16 tiles measured no faster)
-    constexpr int TX = 64, TY = 8, ZC = sizeof(R) == 4 ? 32 : 16;
-    const int tx = (A.nx + TX - 1) / TX, ty = (A.ny3 + TY - 1) / TY;
-    const dim3 grid(tx * ty * ((A.nz + ZC - 1) / ZC)), block(TX * TY);
-    auto kern = k_step3_median<S, TX, TY, ZC>;
-    if (e0 && e1) hipExtLaunchKernelGGL(kern, grid, block, 0, s, e0, e1, 0, A, tx, ty);
-    else hipLaunchKernelGGL(kern, grid, block, 0, s, A, tx, ty);
+    // 64 x 8 columns: 1.29 halo sites per site (FP32 arithmetic: 64 x 16
+    // tiles measured no faster)
+    constexpr int ZC = m3_layers<S>();
+    const int tx = (A.nx + kM3X - 1) / kM3X, ty = (A.ny3 + kM3Y - 1) / kM3Y;
+    const dim3 grid(tx * ty * ((A.nz + ZC - 1) / ZC)), block(kM3X * kM3Y);
+    auto first = k_step3<S, true>;
+    auto second = k_step3_median<S, kM3X, kM3Y, ZC>;
+    if (e0) (void)hipEventRecord(e0, s);
+    hipLaunchKernelGGL(first, rows, dim3(256), 0, s, A);
+    hipLaunchKernelGGL(second, grid, block, 0, s, A, tx, ty);
+    if (e1) (void)hipEventRecord(e1, s);
   } else {
-    const dim3 grid((unsigned)((A.nx + 255) / 256 * (long long)A.ny3 * A.nz)), block(256);
-    if (e0 && e1) hipExtLaunchKernelGGL(k_step3<S>, grid, block, 0, s, e0, e1, 0, A);
-    else hipLaunchKernelGGL(k_step3<S>, grid, block, 0, s, A);
+    auto kern = k_step3<S, false>;
+    if (e0 && e1) hipExtLaunchKernelGGL(kern, rows, dim3(256), 0, s, e0, e1, 0, A);
+    else hipLaunchKernelGGL(kern, rows, dim3(256), 0, s, A);
   }
   return hipGetLastError();
+}
+
+long long med3_chunks(int storage, int nx, int ny, int nz) {
+  const int zc = storage == 0 ? m3_layers<double>() : m3_layers<float>();
+  return (long long)((nx + kM3X - 1) / kM3X) * ((ny + kM3Y - 1) / kM3Y) * ((nz + zc - 1) / zc);
 }
 
 hipError_t launch_step3(int storage, bool median, const void* args, hipStream_t s, hipEvent_t e0,
