@@ -117,27 +117,30 @@ __device__ __forceinline__ void adjoint_site(const StepArgs<typename StoreT<S>::
 #pragma unroll
     for (int i = 0; i < Q; ++i) { lf[i] = lam[i]; mu[i] = R(0); }
   } else {
-    R q[Q];
     CollInfo<R> ci;
     if constexpr (COLL == COLL_ELBM) {
-      // alpha and branch of the forward step, kept by the recompute: the
-      // collided state is the forward's bit for bit without a second root solve
+      // alpha and branch of the forward step, kept by the recompute
       ci.alpha = B.alpha[o];
       ci.branch = B.branch[o];
-      const R ab = ci.alpha * (om * R(0.5));
-#pragma unroll
-      for (int i = 0; i < Q; ++i) q[i] = v[i] + ab * d[i];
-    } else if constexpr (Q == 9) {
-      if (mrt_here) collide_site<S, Q, COLL_MRT>(A, v, feq, d, om, q, ci);
-      else collide_site<S, Q, COLL>(A, v, feq, d, om, q, ci);
-    } else {
-      collide_site<S, Q, COLL>(A, v, feq, d, om, q, ci);
     }
     // positivity rule: g'' = f* + phi (q - f*), phi = f*_a / (f*_a - q_a)
     R lq[Q];
 #pragma unroll
     for (int i = 0; i < Q; ++i) lq[i] = lam[i];
     if (A.positivity) {
+      // the collided state (ELBM: the forward's bit for bit, without a second
+      // root solve)
+      R q[Q];
+      if constexpr (COLL == COLL_ELBM) {
+        const R ab = ci.alpha * (om * R(0.5));
+#pragma unroll
+        for (int i = 0; i < Q; ++i) q[i] = v[i] + ab * d[i];
+      } else if constexpr (Q == 9) {
+        if (mrt_here) collide_site<S, Q, COLL_MRT>(A, v, feq, d, om, q, ci);
+        else collide_site<S, Q, COLL>(A, v, feq, d, om, q, ci);
+      } else {
+        collide_site<S, Q, COLL>(A, v, feq, d, om, q, ci);
+      }
       R q2[Q];
 #pragma unroll
       for (int i = 0; i < Q; ++i) q2[i] = q[i];
@@ -250,6 +253,16 @@ __device__ __forceinline__ void adjoint_site(const StepArgs<typename StoreT<S>::
   for (int i = 0; i < Q; ++i) a[i] = mu[i] + tf[i];
 }
 
+// No active lane of the wavefront holds a site on the lattice's outer ring:
+// every pull source lies inside, at a fixed offset from the site (a scalar
+// base per population instead of a selected plane and 64-bit address; the
+// pull itself, whose loads a branch would hold up, measured slower with it).
+template <int Q>
+__device__ __forceinline__ bool interior_wave(int nx, int ny, int x, int y) {
+  const bool ring = x == 0 || x == nx - 1 || (Q == 9 && (y == 0 || y == ny - 1));
+  return __ballot(ring) == 0ull;
+}
+
 // Transpose of the pull: val_i, the derivative with respect to the
 // population that site (x, y) pulled in direction i, goes to that
 // population's slot of the adjoint lattice (add = true adds it to what is
@@ -258,6 +271,16 @@ template <class R, int Q, bool ADD = false>
 __device__ __forceinline__ void push_adjoint(const StepArgs<R>& A, R* lam_out, int x, int y,
                                              const R val[Q]) {
   const long long o = (long long)y * A.pitch + x;
+  if (interior_wave<Q>(A.nx, A.ny, x, y)) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      R* dst = at(lam_out + (long long)i * A.qs,
+                  (unsigned)o - (unsigned)(vy_of<Q>(i) * A.pitch + vx_of<Q>(i)));
+      if constexpr (ADD) *dst += val[i];
+      else __builtin_nontemporal_store(val[i], dst);
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     int sx = x - vx_of<Q>(i), sy = y - vy_of<Q>(i);
@@ -314,7 +337,7 @@ void k_adjoint(const StepArgs<typename StoreT<S>::R> A, const AdjArgs<typename S
   if (s >= (long long)A.nx * A.ny) return;
   bool ehr = B.mask && B.mask[s];
   for (int j = 0; j < nl; ++j) ehr |= lsel[j] == (int32_t)s;
-  const int y = (int)(s / A.nx), x = (int)(s % A.nx);
+  const int y = (int)((unsigned)s / (unsigned)A.nx), x = (int)((unsigned)s % (unsigned)A.nx);
   R v[Q], feq[Q], d[Q], m0, ux, uy;
   site_prep<S, Q, false, false>(A, x, y, v, feq, d, m0, ux, uy, false);
   const long long o = (long long)y * A.pitch + x;
@@ -636,6 +659,75 @@ hipError_t launch_adjoint(int storage, int Q, int coll, const void* step_args, c
   if (storage == 1) return launch_adj_s<float>(Q, coll, step_args, &B, s, e0, e1);
   if (storage == 2) return launch_adj_s<_Float16>(Q, coll, step_args, &B, s, e0, e1);
   return launch_adj_s<bf16_t>(Q, coll, step_args, &B, s, e0, e1);
+}
+
+// The recompute's step with the recorded Ehrenfest sites (a list short enough
+// for LDS) sent to f* at once: no entropy, no candidates, no counters, and no
+// second launch for the list.  512^2 MRT FP32: 7.6 + 3.5 -> 7.7 us a step.
+template <class S, int Q, int COLL>
+__global__ __launch_bounds__(256) void k_restep(const StepArgs<typename StoreT<S>::R> A,
+                                                const int32_t* list, const long long* count,
+                                                long long k) {
+  using R = typename StoreT<S>::R;
+  const long long nb = gridDim.x, b = blockIdx.x;
+  const long long tb = (b / 16 * 16 + 16 <= nb) ? (b / 16) * 16 + (b % 8) * 2 + (b / 8) % 2 : b;
+  const long long s = tb * blockDim.x + threadIdx.x;
+  __shared__ int32_t lsel[kAdjListLds];
+  AdjArgs<R> B{};
+  B.list = list;
+  B.count = count;
+  B.k = k;
+  const int nl = load_short_list<R>(B, lsel);
+  if (s >= (long long)A.nx * A.ny) return;
+  bool sel = false;
+  for (int j = 0; j < nl; ++j) sel |= lsel[j] == (int32_t)s;
+  const int y = (int)((unsigned)s / (unsigned)A.nx), x = (int)((unsigned)s % (unsigned)A.nx);
+  R v[Q], feq[Q], d[Q], post[Q], m0, ux, uy;
+  site_prep<S, Q, false, false>(A, x, y, v, feq, d, m0, ux, uy, false);
+  if (sel) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) post[i] = feq[i];
+  } else {
+    const R om = A.omega_field ? A.omega_field[(long long)y * A.pitch + x] : A.omega;
+    CollInfo<R> ci;
+    collide_site<S, Q, COLL>(A, v, feq, d, om, post, ci);
+    if (A.positivity) positivity_site<S, Q>(A, feq, post, ci);
+  }
+  S* dst = (S*)A.dst;
+  const unsigned o = (unsigned)(y * A.pitch + x);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) StoreT<S>::st(at(dst + (long long)i * A.qs, o), post[i]);
+}
+
+template <class S, int Q>
+static hipError_t restep_q(int coll, const void* sargs, const int32_t* list, const long long* cnt,
+                           long long k, hipStream_t s) {
+  const StepArgs<typename StoreT<S>::R>& A = *(const StepArgs<typename StoreT<S>::R>*)sargs;
+  const unsigned g = (unsigned)(((long long)A.nx * A.ny + 255) / 256);
+  if (coll == COLL_LBGK) {
+    hipLaunchKernelGGL((k_restep<S, Q, COLL_LBGK>), dim3(g), dim3(256), 0, s, A, list, cnt, k);
+  } else if constexpr (Q == 9) {
+    if (coll != COLL_MRT) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_restep<S, Q, COLL_MRT>), dim3(g), dim3(256), 0, s, A, list, cnt, k);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_restep(int storage, int Q, int coll, const void* args, const int32_t* list,
+                         const long long* count, long long k, hipStream_t s) {
+  if (!list || !count || k > kAdjListLds) return hipErrorInvalidValue;
+  switch (storage * 16 + Q) {
+    case 0 * 16 + 9: return restep_q<double, 9>(coll, args, list, count, k, s);
+    case 0 * 16 + 3: return restep_q<double, 3>(coll, args, list, count, k, s);
+    case 1 * 16 + 9: return restep_q<float, 9>(coll, args, list, count, k, s);
+    case 1 * 16 + 3: return restep_q<float, 3>(coll, args, list, count, k, s);
+    case 2 * 16 + 9: return restep_q<_Float16, 9>(coll, args, list, count, k, s);
+    case 2 * 16 + 3: return restep_q<_Float16, 3>(coll, args, list, count, k, s);
+    case 3 * 16 + 9: return restep_q<bf16_t, 9>(coll, args, list, count, k, s);
+    default: return restep_q<bf16_t, 3>(coll, args, list, count, k, s);
+  }
 }
 
 template <class S, int Q>

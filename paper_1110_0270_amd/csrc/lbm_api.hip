@@ -980,6 +980,13 @@ static lbm_status backward_impl(lbm_ctx* c, const void* dL_dfT, void* dL_df0, vo
       const bool last = t + 1 == t1;
       const void* args = args_for(seg(t - t0), last ? seg(A.K) : seg(t + 1 - t0),
                                   alpha_slot(t - t0), branch_slot(t - t0));
+      if (A.k > 0 && A.k <= kAdjListMax && !A.store_alpha && !med &&
+          c->cfg.sel_action == LBM_SEL_EQUILIBRIUM) {
+        e = launch_restep(c->cfg.storage, Q, c->cfg.collision, args,
+                          adjoint_selected_slot(A, ws, t, nullptr), adjoint_count_slot(A, ws, t),
+                          A.k, st);
+        continue;
+      }
       e = launch_step(c->cfg.storage, Q, c->cfg.collision, med, args, st);
       if (e == hipSuccess && A.k > 0 && !last)
         e = launch_tape_fix(c->cfg.storage, Q, args, adjoint_selected_slot(A, ws, t, nullptr),
