@@ -40,6 +40,7 @@ struct Layout {
   size_t lat_bytes = 0;
   int rows = 0;            // ny, or nz * ny for D3Q27
   size_t off_nl = 0;       // nonlocal filter coefficients (27 values of the compute type)
+  size_t clear_bytes = 0;  // lbm_step_noalloc: the clear part at the front
   size_t off_med3 = 0, med3_bytes = 0;  // D3Q27 median step: Med3State and the chunk records
   size_t off_lat[2] = {0, 0}, off_omega = 0, off_sel = 0, off_cnt = 0, off_partial = 0,
          off_stats = 0, off_div = 0, off_ckey = 0, off_cidx = 0, off_cmom = 0, off_hist = 0,
@@ -158,8 +159,17 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
   }
   L.off_omega = c->omega_field ? take((size_t)L.qs * rb) : 0;
   L.off_sel = take(sizeof(SelState));
+  if (!lattices) {
+    // lbm_step_noalloc: what a step expects clear lies at the same place for
+    // every configuration, where the previous call left it clear
+    L.off_hist = take((size_t)kHistWords * 4);
+    L.off_coarse = take(kCoarse * 4);
+    L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
+    L.off_f64cnt = take(2 * sizeof(unsigned int));
+    L.clear_bytes = o;
+  }
   L.off_cnt = take((size_t)kCntSlots * CNT_N * sizeof(unsigned long long));
-  L.off_partial = take(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
+  if (lattices) L.off_partial = take(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
   L.off_nl = c->nl_filter ? take(27 * rb) : 0;
   if (L.Q == 27 && (c->limiters & LBM_LIM_MEDIAN)) {
     L.med3_bytes = sizeof(Med3State) + (size_t)med3_chunks(c->storage, c->nx, c->ny, c->nz) * sizeof(Med3Chunk);
@@ -177,9 +187,11 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
     L.off_cidx = take((size_t)L.cap * 4);
     L.off_cmom = take((size_t)L.cap * 3 * rb);
     L.off_wcount = take((size_t)tiles * 4 * 4);
-    L.off_hist = take((size_t)kHistWords * 4);
-    L.off_coarse = take(kCoarse * 4);
-    L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
+    if (lattices) {
+      L.off_hist = take((size_t)kHistWords * 4);
+      L.off_coarse = take(kCoarse * 4);
+      L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
+    }
     // kSweepRegions regions x 64 entries per sweep workgroup
     L.off_stage = take((size_t)((tiles * 4 + kSweepRegions - 1) / kSweepRegions) * kSweepRegions * 64 * 4);
     L.bcap = std::min<long long>(L.cap, 1ll << 20);
@@ -188,7 +200,7 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
   }
   if (c->collision == LBM_ELBM && !is_f64(c->storage)) {
     L.off_f64list = take((size_t)L.n_sites * 4);
-    L.off_f64cnt = take(2 * sizeof(unsigned int));
+    if (lattices) L.off_f64cnt = take(2 * sizeof(unsigned int));
   }
   if (c->ens_limiter != LBM_ENS_NONE) {
     L.off_ens = take(sizeof(EnsState));
@@ -1047,35 +1059,18 @@ hipError_t scratch_address(int dev, void** out) {
   return hipSuccess;
 }
 
-// Everything a step reads before writing it, cleared in the scratch array
-// with a kernel (no memset nodes when the caller captures the call): the
-// selection state (its floor back at the threshold), the histograms, the
-// candidate counters and region counts, the limiter counters and the FP64
-// site list's count.
-struct ScratchReset {
-  SelState sel;
-  SelState* sel_dst;
-  unsigned long long* counters;   // kCntSlots * CNT_N
-  unsigned int* hist;             // kHistWords
-  unsigned int* coarse;           // kCoarse
-  unsigned long long* ccount;     // kCountSlots * kCountStride
-  uint32_t* wcount;               // n_wcount
-  long long n_wcount;
-  unsigned int* f64_count;        // 2
-};
+// The front of the scratch array (selection state, histograms, candidate
+// counters, the FP64 site list's count) is clear between calls: it is when the
+// library is loaded (static device memory), and a call's last kernel leaves it
+// so, whatever it found.  Only a call that failed to enqueue all its kernels
+// may not have: the next one clears it with a kernel first (no memset nodes
+// when the caller captures the call), and one that is being captured leaves
+// that to the next call outside a capture as well.
+bool g_scratch_dirty[kMaxDevices] = {};
 
-__global__ void k_scratch_reset(const ScratchReset r) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long stride = (long long)gridDim.x * blockDim.x;
-  if (t == 0) *r.sel_dst = r.sel;
-  for (long long i = t; i < (long long)kCntSlots * CNT_N; i += stride) r.counters[i] = 0;
-  if (r.hist) {
-    for (long long i = t; i < kHistWords; i += stride) r.hist[i] = 0;
-    for (long long i = t; i < kCoarse; i += stride) r.coarse[i] = 0;
-    for (long long i = t; i < (long long)kCountSlots * kCountStride; i += stride) r.ccount[i] = 0;
-    for (long long i = t; i < r.n_wcount; i += stride) r.wcount[i] = 0;
-  }
-  if (r.f64_count && t < 2) r.f64_count[t] = 0;
+__global__ void k_scratch_clear(uint4* p, int n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 }  // namespace
@@ -1122,21 +1117,24 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
     args = &a32;
   }
   const bool ehr = (cfg->limiters & LBM_LIM_EHRENFEST) != 0;
-  ScratchReset r;
-  std::memset((void*)&r, 0, sizeof(r));
-  init_select_state(&r.sel, f64);
-  r.sel_dst = (SelState*)(ws + L.off_sel);
-  r.counters = (unsigned long long*)(ws + L.off_cnt);
-  if (ehr) {
-    r.hist = (unsigned int*)(ws + L.off_hist);
-    r.coarse = (unsigned int*)(ws + L.off_coarse);
-    r.ccount = (unsigned long long*)(ws + L.off_ccount);
-    r.wcount = (uint32_t*)(ws + L.off_wcount);
-    r.n_wcount = L.cap / 64;
+  // no counters are reported, and no floor is carried from call to call
+  a64.no_carry = a32.no_carry = 1;
+  a64.count_events = a32.count_events = 0;
+  bool was_dirty;
+  {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    was_dirty = g_scratch_dirty[dev];
+    g_scratch_dirty[dev] = true;
   }
-  r.f64_count = L.off_f64cnt ? (unsigned int*)(ws + L.off_f64cnt) : nullptr;
-  hipLaunchKernelGGL(k_scratch_reset, dim3(64), dim3(256), 0, st, r);
-  e = hipGetLastError();
+  bool stays_dirty = false;
+  if (was_dirty) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(st, &cs);
+    if (e != hipSuccess) return hip_fail(e, "lbm_step_noalloc");
+    stays_dirty = cs != hipStreamCaptureStatusNone;
+    hipLaunchKernelGGL(k_scratch_clear, dim3(8), dim3(256), 0, st, (uint4*)ws, (int)(L.clear_bytes / 16));
+    e = hipGetLastError();
+  }
   if (e == hipSuccess)
     e = launch_step(cfg->storage, L.Q, cfg->collision, (cfg->limiters & LBM_LIM_MEDIAN) != 0,
                     args, st);
@@ -1156,6 +1154,10 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
     e = launch_select(sa, st);
   }
   if (e != hipSuccess) return hip_fail(e, "lbm_step_noalloc");
+  if (!stays_dirty) {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_scratch_dirty[dev] = false;
+  }
   return LBM_OK;
 }
 

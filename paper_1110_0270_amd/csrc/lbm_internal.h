@@ -125,6 +125,7 @@ struct StepArgs {
   int positivity;
   int ehrenfest;
   int count_events;
+  int no_carry;          // the selection starts from its threshold, whatever SelState holds
   R rho0;
   R omega;
   const R* omega_field;  // [ny][pitch] or nullptr

@@ -313,7 +313,7 @@ __device__ void append_sites(const StepArgs<typename StoreT<S>::R>& A, int wg, i
   const SelState* st = A.sel;
   const unsigned int fb = (unsigned int)st->fb_bin;
   const R screen = value_of_key<R>(coarse_edge_key<R>((int)fb));
-  StepFrame fr = step_frame(st);
+  const StepFrame fr = step_frame<R>(A);
   const int T = A.tiles_x * A.tiles_y;
   const int w = threadIdx.x / 64, lane = threadIdx.x % 64, per = (int)blockDim.x / 256;
   for (int t = wg * per + w / 4; t < T; t += nwg * per) {
@@ -395,8 +395,8 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
                          int32_t* selected, uint32_t* blist, long long bcap,
                          long long* n_sel_out, int32_t* tape_sel, long long* tape_cnt,
                          long long tape_len, uint32_t* scratch, long long scratch_len,
-                         const Boundary& bd, unsigned long long sel_bnd, unsigned int* h,
-                         bool have_h, SelScratch& lds) {
+                         const Boundary& bd, const StepFrame& fr, unsigned long long sel_bnd,
+                         unsigned int* h, bool have_h, SelScratch& lds) {
   using R = typename StoreT<S>::R;
   SelState* st = A.sel;
   __shared__ unsigned int dh[256];
@@ -409,8 +409,6 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   // every load is issued before the first barrier; both parities' fields
   // are loaded with the step count (one round trip)
   const unsigned long long step = st->step;
-  const unsigned long long base_p[2] = {st->base_key[0], st->base_key[1]};
-  const unsigned int shift_p[2] = {st->shift[0], st->shift[1]};
   const int raised_p[2] = {st->floor_raised[0], st->floor_raised[1]};
   const unsigned long long floor_p[2] = {st->floor_key[0], st->floor_key[1]};
   if (!have_h) load_hist(A.hist, h);
@@ -432,8 +430,8 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   if (threadIdx.x == 0) s_tot = (unsigned int)(sel_bnd >> 32);
   __syncthreads();
   const int par = (int)(step & 1ull);
-  const unsigned long long base = par ? base_p[1] : base_p[0];
-  const unsigned int shift = par ? shift_p[1] : shift_p[0];
+  const unsigned long long base = fr.base;
+  const unsigned int shift = fr.shift;
   const bool raised = (par ? raised_p[1] : raised_p[0]) != 0;
   const unsigned long long floor_prev = par ? floor_p[1] : floor_p[0];
   const long long need = k < nc ? k : nc;
@@ -447,7 +445,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     // counted by `slices` threads, each against a contiguous slice of the
     // list in LDS; the entries of rank below `take` are selected.  The
     // moments are loaded with the key, so f* needs no further round trip.
-    const unsigned long long edge = base + ((unsigned long long)boundary << shift);
+    const unsigned long long edge = boundary ? base + ((unsigned long long)boundary << shift) : 0ull;
     const int mq = (int)((m + 63) & ~63ll);          // entries rounded up to whole wavefronts
     const int slices = (int)blockDim.x / mq;         // >= 4
     const int q = (int)threadIdx.x % mq, sl = (int)threadIdx.x / mq;
@@ -488,9 +486,9 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     if (sel && (long long)slot < k) selected[slot] = (int32_t)~nq;
   } else if (take > 0 && m > 0) {
     // keys of the bucket differ only in their offset from its lower edge:
-    // `shift` bits, or all bits in the open-ended top bucket
-    const unsigned long long edge = base + ((unsigned long long)boundary << shift);
-    const int nb = boundary == kBuckets - 1 ? KeyTraits<R>::bits : (int)shift;
+    // `shift` bits, or all bits in the open-ended first and last buckets
+    const unsigned long long edge = boundary ? base + ((unsigned long long)boundary << shift) : 0ull;
+    const int nb = boundary == kBuckets - 1 || boundary == 0 ? KeyTraits<R>::bits : (int)shift;
     const int kd = (nb + 7) / 8;
     // MSD radix select, one byte per pass: the key digits from the top, then
     // the site index digits.  Up to kTailStage entries are read from the
@@ -709,8 +707,11 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
       int t2;
       unsigned long long a2;
       find_from_top<kBuckets, true>(h, 3ull * (unsigned long long)k, &t2, &a2);
-      if (t2 >= 0 && t2 < kBuckets - 1) fnext = base + ((unsigned long long)t2 << shift);
-      else if (t2 < 0) fnext = base > 2 * KeyTraits<R>::quarter ? base - 2 * KeyTraits<R>::quarter : 0ull;
+      // (bucket 0 may hold keys below the frame: the floor stays under them)
+      const unsigned long long from = fell_back ? base : floor_prev;
+      if (t2 > 0 && t2 < kBuckets - 1) fnext = base + ((unsigned long long)t2 << shift);
+      else if (t2 == 0) fnext = from;
+      else if (t2 < 0) fnext = from > 2 * KeyTraits<R>::quarter ? from - 2 * KeyTraits<R>::quarter : 0ull;
       else fnext = floor_prev;
     }
     if (fnext < dk) fnext = dk;
@@ -738,10 +739,16 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     const unsigned long long span = (unsigned long long)kBuckets << shift;
     const unsigned long long hi_key = s_top < 0 ? fnext + 1
         : (s_top < kBuckets - 1 ? base + ((unsigned long long)(s_top + 1) << shift) : base + 2 * span);
-    st->floor_key[par] = fnext;
-    st->floor_raised[par] = fnext > dk ? 1 : 0;
-    st->base_key[par] = fnext;
-    st->shift[par] = frame_shift(fnext, hi_key > fnext ? fnext + 2 * (hi_key - fnext) : fnext + 1);
+    if (!A.no_carry) {
+      st->floor_key[par] = fnext;
+      st->floor_raised[par] = fnext > dk ? 1 : 0;
+      // (a floor at the threshold 0 would spread the frame over every octave
+      // there is: at most 60 below the top, the rest in bucket 0)
+      const unsigned long long low = hi_key > 60 * FirstFrame<R>::octave ? hi_key - 60 * FirstFrame<R>::octave : 0ull;
+      const unsigned long long fb = fnext > low ? fnext : low;
+      st->base_key[par] = fb;
+      st->shift[par] = frame_shift(fb, hi_key > fb ? fb + 2 * (hi_key - fb) : fb + 1);
+    }
     const unsigned int ns = s_tot < (unsigned int)k ? s_tot : (unsigned int)k;
     st->n_sel = (long long)ns;
     if (n_sel_out) *n_sel_out = (long long)ns;
@@ -924,13 +931,14 @@ __device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A
 
 template <class S, int Q>
 __device__ __forceinline__ void tail_of(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a,
-                                        const Boundary& bd, unsigned long long sel_bnd,
+                                        const Boundary& bd, const StepFrame& fr,
+                                        unsigned long long sel_bnd,
                                         unsigned int* h, bool have_h, SelScratch& lds) {
   // the region sweep's stage (one entry per candidate slot) serves as the
   // exact resolution's scratch
   fix_tail<S, Q>(A, a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
                  a.tape_cnt, a.tape_len, (uint32_t*)a.stage,
-                 (long long)a.nchunk * kSweepRegions * 64, bd, sel_bnd, h, have_h, lds);
+                 (long long)a.nchunk * kSweepRegions * 64, bd, fr, sel_bnd, h, have_h, lds);
 }
 
 __device__ __forceinline__ int32_t* selected_slot(const TailArgs& a, const SelState* st) {
@@ -952,7 +960,7 @@ __global__ __launch_bounds__(kSweepRegions) void k_sel_sweep(const StepArgs<type
   const long long my_r = sweep_region(blockIdx.x, a.nchunk);
   const uint32_t cnt =
       sweeps && my_r < (long long)A.tiles_x * A.tiles_y * 4 ? A.wcount[my_r] : 0u;
-  const StepFrame fr = step_frame(st);
+  const StepFrame fr = step_frame<R>(A);
   const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
   const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
   int32_t* selected = selected_slot(a, st);
@@ -986,18 +994,20 @@ __global__ __launch_bounds__(1024) void k_sel_tail(const StepArgs<typename Store
   const int fallback = st->fallback;
   Boundary bd{(long long)st->b_nc, st->b_bin, st->b_above};
   unsigned long long sel_bnd = st->sel_bnd;
+  StepFrame fr = step_frame<R>(A);
   if (fallback) {
     append_sites<S, Q>(A, blockIdx.x, gridDim.x);
     if (!last_block(&st->ticket)) return;
     if (threadIdx.x == 0) st->ticket = 0;
     bd = boundary_from(h, load_counts<R>(A, h), a.k);
-    sel_bnd = sweep_all<S, Q>(A, a, bd, step_frame(st), selected_slot(a, st));
+    fr = step_frame<R>(A);
+    sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected_slot(a, st));
     __threadfence();
     __syncthreads();
   } else if (blockIdx.x != 0) {
     return;
   }
-  tail_of<S, Q>(A, a, bd, sel_bnd, h, fallback != 0, lds);
+  tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, fallback != 0, lds);
 }
 
 // The whole selection of a small lattice by one workgroup.
@@ -1010,7 +1020,7 @@ __global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT
   __shared__ SelScratch lds;
   const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
   const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
-  StepFrame fr = step_frame(st);
+  StepFrame fr = step_frame<R>(A);
   int32_t* selected = selected_slot(a, st);
   long long nc = load_counts<R>(A, h);
   if (nc < a.k && raised) {
@@ -1024,14 +1034,14 @@ __global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT
     append_sites<S, Q>(A, 0, 1);
     __threadfence();
     __syncthreads();
-    fr = step_frame(st);
+    fr = step_frame<R>(A);
     nc = load_counts<R>(A, h);
   }
   const Boundary bd = boundary_from(h, nc, a.k);
   const unsigned long long sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected);
   __threadfence();
   __syncthreads();
-  tail_of<S, Q>(A, a, bd, sel_bnd, h, true, lds);
+  tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, true, lds);
 }
 
 // The MRT limiter (section 5) on an LBGK lattice: the step's selected sites,
@@ -1124,11 +1134,11 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
   }
 }
 
-// Initial selection state: floor at the threshold, a frame spanning every
-// positive key (bucket = the top 12 bits of the key).
+// Initial selection state: floor at the threshold, and the first frame.
 void init_select_state(SelState* h, int f64) {
   *h = SelState{};
-  h->shift[0] = h->shift[1] = f64 ? 51u : 19u;
+  h->base_key[0] = h->base_key[1] = f64 ? FirstFrame<double>::base : FirstFrame<float>::base;
+  h->shift[0] = h->shift[1] = f64 ? FirstFrame<double>::shift : FirstFrame<float>::shift;
 }
 
 }  // namespace lbm

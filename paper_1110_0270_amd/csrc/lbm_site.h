@@ -400,6 +400,22 @@ __device__ __forceinline__ int bucket_of(unsigned long long key, unsigned long l
   return b >= (unsigned long long)kBuckets ? kBuckets - 1 : (int)b;
 }
 
+// Histogram frame of a step without a carried one: 64 buckets per octave of
+// Delta S from 2^-60 up (the top 12 bits of the key, two per octave, left
+// hundreds of sites of a small lattice in the boundary bucket).  Keys below
+// the frame share bucket 0, which the tail resolves by their whole bits.
+template <class R> struct FirstFrame;
+template <> struct FirstFrame<float> {
+  static constexpr unsigned long long base = (127ull - 60) << 23;
+  static constexpr unsigned int shift = 23 - 6;
+  static constexpr unsigned long long octave = 1ull << 23;
+};
+template <> struct FirstFrame<double> {
+  static constexpr unsigned long long base = (1023ull - 60) << 52;
+  static constexpr unsigned int shift = 52 - 6;
+  static constexpr unsigned long long octave = 1ull << 52;
+};
+
 // Candidate floor and histogram frame of this step's parity.  Both
 // parities' fields and the step count are read unconditionally (the state
 // always exists), so that the loads issue together.
@@ -407,11 +423,14 @@ struct StepFrame {
   unsigned long long floor, base;
   unsigned int shift;
 };
-__device__ __forceinline__ StepFrame step_frame(const SelState* sel) {
+template <class R>
+__device__ __forceinline__ StepFrame step_frame(const StepArgs<R>& A) {
+  const SelState* sel = A.sel;
   const unsigned long long f0 = sel->floor_key[0], f1 = sel->floor_key[1];
   const unsigned long long b0 = sel->base_key[0], b1 = sel->base_key[1];
   const unsigned int s0 = sel->shift[0], s1 = sel->shift[1];
   const bool odd = (sel->step & 1ull) != 0;
+  if (A.no_carry) return StepFrame{0ull, FirstFrame<R>::base, FirstFrame<R>::shift};
   return StepFrame{odd ? f1 : f0, odd ? b1 : b0, odd ? s1 : s0};
 }
 
@@ -440,8 +459,12 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
                                                   typename KeyOf<R>::T key, uint32_t idx,
                                                   R m0, R ux, R uy) {
   const unsigned long long mask = __ballot(is_c);
-  if (!mask) return;
   const int lane = __lane_id();
+  // (the counts of a carried selection are left clear by the previous step;
+  // stacked tiles may reach past the last region)
+  if (A.no_carry && !mask && lane == 0 && region < (long long)A.tiles_x * A.tiles_y * 4)
+    A.wcount[region] = 0u;
+  if (!mask) return;
   if (lane == __ffsll((long long)mask) - 1) {
     A.wcount[region] = (uint32_t)__popcll(mask);
     atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));

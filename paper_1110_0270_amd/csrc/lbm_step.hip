@@ -166,7 +166,7 @@ void k_step(const StepArgs<typename StoreT<S>::R> A) {
   // the median filter, sites provably below delta as well (below both,
   // a site is no candidate of either), and a workgroup that holds a
   // median candidate evaluates them exactly further down.
-  const StepFrame fr = step_frame(A.sel);
+  const StepFrame fr = step_frame<R>(A);
   const R ehr_screen = A.ehrenfest ? value_of_key<R>(fr.floor) : r_inf<R>();
   const R screen = ENS ? R(0)
                        : (MEDIAN ? fmin(A.med_delta, ehr_screen) : (A.ehrenfest ? ehr_screen : R(0)));
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256, (COLL == COLL_LBGK && sizeof(S) == 2) ? 8 : 1)
   const unsigned c[3] = {(unsigned)(xl == A.nx - 1 ? 0 : xl + 1), (unsigned)xl,
                          (unsigned)(xl == 0 ? A.nx - 1 : xl - 1)};   // source columns, a = -1, 0, +1
   unsigned long long* const cnt = A.counters + (blockIdx.x % kCntSlots) * CNT_N;
-  const StepFrame fr = step_frame(A.sel);
+  const StepFrame fr = step_frame<R>(A);
   const R screen = (EHR && A.ehrenfest) ? value_of_key<R>(fr.floor) : R(0);
   const S* __restrict__ src = (const S*)A.src;
 
