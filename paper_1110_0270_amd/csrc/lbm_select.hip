@@ -888,10 +888,12 @@ __device__ void sweep_chunk(const StepArgs<typename StoreT<S>::R>& A, const Tail
 
 // The whole region sweep by one workgroup (small lattices, and the step after
 // a rescan): its LDS counters are the lists' slots.  Returns both counts
-// (SelState::sel_bnd's layout).
+// (SelState::sel_bnd's layout); what it wrote is read by this workgroup only,
+// whose wavefronts share the L1, so the barrier at the end orders it.
 template <class S, int Q>
 __device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a,
                                         const Boundary& bd, const StepFrame& fr, int32_t* selected) {
+  using R = typename StoreT<S>::R;
   __shared__ unsigned int s_sel, s_bnd;
   if (threadIdx.x == 0) { s_sel = 0; s_bnd = 0; }
   __syncthreads();
@@ -900,6 +902,23 @@ __device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A
   // different wavefronts)
   const int mine = (int)(threadIdx.x % 64) * (int)(blockDim.x / 64) + (int)(threadIdx.x / 64);
   const long long nreg = (long long)A.tiles_x * A.tiles_y * 4;
+  // an entry whose key has been loaded: the rest of it only where it is
+  // selected (of a small lattice's candidates hardly any are)
+  auto take = [&](bool on, unsigned long long key, long long p) {
+    const int b = bucket_of<R>(key, fr.base, fr.shift);
+    const bool sel = on && (bd.bin < 0 || b > bd.bin), bnd = on && b == bd.bin;
+    if (__ballot(sel)) {
+      uint32_t idx = 0;
+      if (sel) {
+        idx = A.cand_idx[p];
+        write_feq_at<S, Q>(A, idx, A.cand_mom[p], A.cand_mom[A.cap + p], A.cand_mom[2 * A.cap + p]);
+      }
+      const unsigned int slot = lds_slot(sel, &s_sel);
+      if (sel && (long long)slot < a.k) selected[slot] = (int32_t)idx;
+    }
+    const unsigned int q = lds_slot(bnd, &s_bnd);
+    if (bnd && (long long)q < a.bcap) a.blist[q] = (uint32_t)p;
+  };
   for (long long r0 = 0; r0 < nreg; r0 += (long long)U * blockDim.x) {
     uint32_t cnt[U];
 #pragma unroll
@@ -912,16 +931,37 @@ __device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A
       uint32_t c = cnt[0];
 #pragma unroll
       for (int q = 1; q < U; ++q) c = u == q ? cnt[q] : c;
-      if (!__ballot(c != 0)) continue;
+      unsigned long long nz = __ballot(c != 0);
+      if (!nz) continue;
       const long long r = r0 + (long long)u * blockDim.x + mine;
-      walk_regions(r, c, [&](bool on, long long p) {
-        bool sel, bnd;
-        const uint32_t idx = visit_entry<S, Q>(A, on, p, bd.bin, fr.base, fr.shift, sel, bnd);
-        const unsigned int slot = lds_slot(sel, &s_sel);
-        if (sel && (long long)slot < a.k) selected[slot] = (int32_t)idx;
-        const unsigned int q = lds_slot(bnd, &s_bnd);
-        if (bnd && (long long)q < a.bcap) a.blist[q] = (uint32_t)p;
-      });
+      const int lane = __lane_id();
+      // sparse regions, one lane each: their first entries' keys together
+      const bool sparse = c != 0 && c <= (uint32_t)kFewCand;
+      if (__ballot(sparse)) {
+        unsigned long long key[kFewCand];
+#pragma unroll
+        for (int e = 0; e < kFewCand; ++e)
+          key[e] = sparse && (uint32_t)e < c ? (unsigned long long)A.cand_key[r * 64 + e] : 0ull;
+#pragma unroll
+        for (int e = 0; e < kFewCand; ++e) take(sparse && (uint32_t)e < c, key[e], r * 64 + e);
+      }
+      // dense regions, one lane per entry: four regions' keys in flight
+      nz = __ballot(c > (uint32_t)kFewCand);
+      while (nz) {
+        bool on[4];
+        long long p[4];
+        unsigned long long key[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int j = nz ? __ffsll((long long)nz) - 1 : 0;
+          on[q] = nz != 0 && (uint32_t)lane < __shfl(c, j);
+          p[q] = __shfl(r, j) * 64 + lane;
+          key[q] = on[q] ? (unsigned long long)A.cand_key[p[q]] : 0ull;
+          if (nz) nz &= nz - 1;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) take(on[q], key[q], p[q]);
+      }
       if (c) A.wcount[r] = 0;
     }
   }
@@ -1002,8 +1042,6 @@ __global__ __launch_bounds__(1024) void k_sel_tail(const StepArgs<typename Store
     bd = boundary_from(h, load_counts<R>(A, h), a.k);
     fr = step_frame<R>(A);
     sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected_slot(a, st));
-    __threadfence();
-    __syncthreads();
   } else if (blockIdx.x != 0) {
     return;
   }
@@ -1039,8 +1077,6 @@ __global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT
   }
   const Boundary bd = boundary_from(h, nc, a.k);
   const unsigned long long sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected);
-  __threadfence();
-  __syncthreads();
   tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, true, lds);
 }
 
