@@ -62,14 +62,27 @@ __device__ __forceinline__ unsigned int ld_rlx(const unsigned int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// True in every thread of the last workgroup to arrive.
+// Stores at the device's coherence point, for what the last workgroup to
+// arrive reads.
+template <class T>
+__device__ __forceinline__ void st_dev(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// True in every thread of the last workgroup to arrive, which then sees what
+// the others wrote with device-scope atomics and st_dev: those are complete at
+// the coherence point once the wait has ended, so no workgroup needs a
+// device-scope release (each one writes back its XCD's whole L2, which held up
+// 256 of them: the two launches of a rescan took 196 and 490 us at 4096^2 with
+// them, 130 and 330 without; 86 and 155, 27 and 50 at 1500 x 1001).
+// The last workgroup drops what its own caches hold of those lines.
 __device__ __forceinline__ bool last_block(unsigned int* ticket) {
   __shared__ bool is_last;
-  __threadfence();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) is_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
   __syncthreads();
-  if (is_last) __threadfence();
+  if (is_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   return is_last;
 }
 
@@ -226,8 +239,8 @@ __device__ __forceinline__ typename StoreT<S>::R scan_dS(const StepArgs<typename
 // eligible sites of the workgroup's share of tiles, added to `coarse`.  The
 // workgroup takes tiles in the step kernel's layout, four at a time (no
 // division per site), and wavefront-aggregated LDS atomics (a shear layer's
-// sites crowd into few bins): 4096^2 FP32 550 -> 196 us, and a step that
-// rescans 1.1 -> 0.7 ms.
+// sites crowd into few bins): 4096^2 FP32 550 -> 130 us, and a step that
+// rescans 1.1 -> 0.47 ms.
 template <class S, int Q>
 __device__ void scan_sites(const StepArgs<typename StoreT<S>::R>& A, unsigned int* h,
                            unsigned int* coarse, int wg, int nwg) {
@@ -251,7 +264,7 @@ __device__ void scan_sites(const StepArgs<typename StoreT<S>::R>& A, unsigned in
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kCoarse; i += blockDim.x)
-    if (h[hx(i)]) atomicAdd(&coarse[i], h[hx(i)]);
+    if (h[hx(i)]) atomicAdd(&coarse[hist_pos(i)], h[hx(i)]);   // spread like the histogram
 }
 
 // After every workgroup's scan_sites, by one workgroup: the coarse bin that
@@ -262,7 +275,8 @@ template <class R>
 __device__ void pick_floor_bin(const StepArgs<R>& A, long long k, unsigned int* h,
                                unsigned int* coarse, bool calibrate) {
   SelState* st = A.sel;
-  for (int i = threadIdx.x; i < kCoarse; i += blockDim.x) h[hx(i)] = ld_rlx(&coarse[i]);
+  for (int p = threadIdx.x; p < kCoarse; p += blockDim.x)
+    h[hx(128 * (p % 32) + p / 32)] = ld_rlx(&coarse[p]);
   __syncthreads();
   int b;
   unsigned long long above;
@@ -326,8 +340,22 @@ __device__ void append_sites(const StepArgs<typename StoreT<S>::R>& A, int wg, i
       is_c = (dS > A.ehr_delta) && coarse_bin((float)dS) >= fb;
     }
     const long long region = (long long)t * 4 + w % 4;
-    if (lane == 0 && !__ballot(is_c)) A.wcount[region] = 0;
-    append_candidates<R>(A, fr, region, is_c, key_of<R>(dS), (uint32_t)(y * A.nx + x), m0, ux, uy);
+    const unsigned long long mask = __ballot(is_c);
+    if (lane == 0) {
+      st_dev(&A.wcount[region], (uint32_t)__popcll(mask));
+      if (mask)
+        atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
+    }
+    const typename KeyOf<R>::T key = key_of<R>(dS);
+    if (is_c) {
+      const long long pos = region * 64 + __popcll(mask & ((1ull << lane) - 1ull));
+      st_dev(&A.cand_key[pos], key);
+      st_dev(&A.cand_idx[pos], (uint32_t)(y * A.nx + x));
+      st_dev(&A.cand_mom[pos], m0);
+      st_dev(&A.cand_mom[A.cap + pos], ux);
+      st_dev(&A.cand_mom[2 * A.cap + pos], uy);
+    }
+    hist_add(A.hist, (unsigned int)hist_pos(bucket_of<R>((unsigned long long)key, fr.base, fr.shift)), is_c);
   }
 }
 
