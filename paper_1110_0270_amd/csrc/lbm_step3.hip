@@ -170,6 +170,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     }
   };
   if (!dense && !flagged) {
+    __syncthreads();   // every wavefront has read the mode: the ticket lets it change
     leave(false);
     return;
   }
