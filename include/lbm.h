@@ -341,7 +341,7 @@ lbm_status lbm_profile_backward(lbm_ctx* ctx, const void* dL_dfT, void* dL_df0,
  *   stream: a hipStream_t (NULL = default stream); the call only enqueues.
  * Each call starts the Ehrenfest selection from its threshold (no candidate
  * floor is carried between calls), so it examines every eligible site.
- * The limiter counters are cleared at every call and not reported.
+ * The limiter events are not counted.
  * Errors: LBM_EINVAL (configuration, NULL or equal buffers), LBM_EWORKSPACE
  * when the configuration needs more scratch than the array holds (large
  * lattices with the Ehrenfest limiter or FP32 ELBM: use lbm_init with a

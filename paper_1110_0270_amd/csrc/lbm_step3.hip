@@ -14,12 +14,14 @@
 //   marches along z through a chunk's layers, keeping Delta S of three layers
 //   (the tile plus a one-site halo) in an LDS ring, so that each layer's
 //   Delta S is evaluated once per column, not once per neighbour.
-// Where most chunks hold such a site (delta = 0) the first kernel would be
-// waste: a step that finds more than a quarter of the chunks flagged leaves
-// the next one to k_step3_median alone, until fewer than an eighth hold a
-// candidate (Med3State; the result does not depend on it).  The first kernel's
-// empty launch then costs 17 us (256^3, 1163 -> 1215 us a step at delta = 0,
-// against 1105 -> 665 at delta = 1e-3 in the Taylor-Green vortex).
+// Where most chunks hold such a site the first kernel would be waste: a step
+// that finds more than a quarter of the chunks flagged leaves the next one to
+// k_step3_median alone, until fewer than an eighth hold a candidate (Med3State;
+// the result does not depend on it).  The first kernel's empty launch then
+// costs 17 us; with delta = 0 every site off its equilibrium is a candidate,
+// and it is not launched.  256^3 FP32 Taylor-Green vortex, us a step: 1104 ->
+// 705 at delta = 1e-3 (no site above it), 1156 -> 1183 at 1e-9 (all above it),
+// 1161 -> 1167 at 0.  160^3 FP64: 771 -> 343, 829 -> 841, 828 -> 832.
 #include <hip/hip_ext.h>
 
 #include "lbm_collide.h"
@@ -59,6 +61,9 @@ __device__ __forceinline__ void finish27(const StepArgs<typename StoreT<S>::R>& 
 }
 
 constexpr int kM3X = 64, kM3Y = 8;
+// Every site off its equilibrium is a candidate: the first kernel is not launched
+template <class R>
+__host__ __device__ inline bool med3_always(R delta) { return !(delta > R(0)); }
 // Layers of a chunk: 1.06 layers of Delta S per layer (FP32)
 template <class S> constexpr int m3_layers() { return sizeof(typename StoreT<S>::R) == 4 ? 32 : 16; }
 
@@ -124,13 +129,16 @@ __device__ __forceinline__ R median27(R a[27]) {
   return a[13];
 }
 
-template <class S, int TX, int TY, int ZC>
+// ALL: every chunk is taken (med3_always), without the first kernel and its
+// records.
+template <class S, int TX, int TY, int ZC, bool ALL>
 __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX * TY <= 512) ? 4 : 1) void k_step3_median(const StepArgs<typename StoreT<S>::R> A,
                                                           int tiles_x, int tiles_y) {
   using R = typename StoreT<S>::R;
   constexpr bool SH = StoreT<S>::shifted;
   constexpr int NT = TX * TY, SW = TX + 2, NS = (TX + 2) * (TY + 2);
   __shared__ R ring[3][NS];
+  __shared__ int s_had;   // a candidate in this chunk (not a register of the march)
 
   // Workgroup -> (tile, chunk of layers).  Consecutive workgroups are dealt
   // round-robin to the 8 XCDs; each XCD takes a contiguous band of tiles
@@ -148,14 +156,13 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
   unsigned long long* const cnt = A.counters + (b % kCntSlots) * CNT_N;
 
   // every workgroup reads the mode before it takes its ticket, so the last
-  // one may change it
-  const bool dense = A.med3->dense != 0;
-  const bool flagged = med3_chunk(A.med3)[tb].flag != 0;
+  // one may change it; it and the flag are read again there, not kept
   // one 64-bit atomic: workgroups done (low half), chunks with a candidate (high)
   auto leave = [&](bool had) {
     if (tid != 0) return;
     // the first kernel's positivity events stand where this one did nothing
     Med3Chunk* const chunk_st = med3_chunk(A.med3) + tb;
+    const bool dense = A.med3->dense != 0, flagged = chunk_st->flag != 0;
     const unsigned long long pos = chunk_st->pos_events;
     if (pos && !dense && !flagged) atomicAdd(cnt + CNT_POSITIVITY, pos);
     if (pos) chunk_st->pos_events = 0ull;
@@ -169,12 +176,14 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
       A.med3->tally = 0ull;
     }
   };
-  if (!dense && !flagged) {
-    __syncthreads();   // every wavefront has read the mode: the ticket lets it change
-    leave(false);
-    return;
+  if constexpr (!ALL) {
+    if (!A.med3->dense && !med3_chunk(A.med3)[tb].flag) {
+      __syncthreads();   // every wavefront has read the mode: the ticket lets it change
+      leave(false);
+      return;
+    }
+    if (tid == 0) s_had = 0;   // the first layer's barrier is before the first candidate
   }
-  bool had = false;      // a candidate in this chunk
 
   // Delta S of layer z (periodic) over the tile and its halo into ring slot
   // `slot`; positions beyond the lattice wrap, so ragged tiles need no
@@ -206,7 +215,6 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     // the count, and only wavefronts with an accepted site select the 14th.
     const R dS = valid ? ring[sc][(ly + 1) * SW + lx + 1] : R(0);
     const bool cand = valid && (dS > A.med_delta) && (dS < r_inf<R>());
-    had |= __ballot(cand) != 0ull;
     bool acc = false;
     R med = R(0);
     auto nbr = [&](int k) {
@@ -214,6 +222,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
       return ring[dz < 0 ? sm : (dz > 0 ? sp : sc)][(ly + 1 + dy) * SW + lx + 1 + dx];
     };
     if (__ballot(cand)) {
+      if constexpr (!ALL) s_had = 1;
       int below = 0;
 #pragma unroll
       for (int k = 0; k < 27; ++k) below += nbr(k) < dS ? 1 : 0;
@@ -242,7 +251,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     finish27<S>(A, (unsigned)((z * A.ny3 + y) * A.pitch + x), valid, v, feq, cnt + CNT_POSITIVITY);
     __syncthreads();   // the next layer overwrites the ring slot of z - 1
   }
-  leave(__syncthreads_or(had));
+  if constexpr (!ALL) leave(s_had != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -259,10 +268,15 @@ static hipError_t launch3(bool median, const void* args, hipStream_t s, hipEvent
     const int tx = (A.nx + kM3X - 1) / kM3X, ty = (A.ny3 + kM3Y - 1) / kM3Y;
     const dim3 grid(tx * ty * ((A.nz + ZC - 1) / ZC)), block(kM3X * kM3Y);
     auto first = k_step3<S, true>;
-    auto second = k_step3_median<S, kM3X, kM3Y, ZC>;
+    auto second = k_step3_median<S, kM3X, kM3Y, ZC, false>;
+    auto alone = k_step3_median<S, kM3X, kM3Y, ZC, true>;
     if (e0) (void)hipEventRecord(e0, s);
-    hipLaunchKernelGGL(first, rows, dim3(256), 0, s, A);
-    hipLaunchKernelGGL(second, grid, block, 0, s, A, tx, ty);
+    if (med3_always(A.med_delta)) {
+      hipLaunchKernelGGL(alone, grid, block, 0, s, A, tx, ty);
+    } else {
+      hipLaunchKernelGGL(first, rows, dim3(256), 0, s, A);
+      hipLaunchKernelGGL(second, grid, block, 0, s, A, tx, ty);
+    }
     if (e1) (void)hipEventRecord(e1, s);
   } else {
     auto kern = k_step3<S, false>;
