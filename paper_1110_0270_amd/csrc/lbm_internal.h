@@ -95,10 +95,12 @@ constexpr int kEnsSlots = 64;
 
 // Device state of the D3Q27 median step, followed by one record per chunk of
 // the lattice (lbm_step3.hip): all zero between steps but for `dense`.
+constexpr int kMed3Groups = 16;
 struct Med3State {
-  unsigned long long tally;  // second kernel: workgroups done, and (high half) chunks with a candidate
+  unsigned long long tally;  // second kernel: groups done, and (high half) chunks with a candidate
   int dense;                 // the next step goes to the second kernel alone
-  int pad[5];
+  int pad[29];
+  unsigned long long group[kMed3Groups][16];   // the same of a group's workgroups, a line each
 };
 struct Med3Chunk {
   unsigned long long flag;        // the first kernel found a site that may lie above delta

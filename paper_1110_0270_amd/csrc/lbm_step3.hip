@@ -20,8 +20,8 @@
 // the result does not depend on it).  The first kernel's empty launch then
 // costs 17 us; with delta = 0 every site off its equilibrium is a candidate,
 // and it is not launched.  256^3 FP32 Taylor-Green vortex, us a step: 1104 ->
-// 705 at delta = 1e-3 (no site above it), 1156 -> 1183 at 1e-9 (all above it),
-// 1161 -> 1167 at 0.  160^3 FP64: 771 -> 343, 829 -> 841, 828 -> 832.
+// 694 at delta = 1e-3 (no site above it), 1156 -> 1176 at 1e-9 (all above it),
+// 1161 -> 1161 at 0.  160^3 FP64: 771 -> 336, 829 -> 841-853, 828 -> 832.
 #include <hip/hip_ext.h>
 
 #include "lbm_collide.h"
@@ -155,21 +155,27 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
   const bool valid = x < A.nx && y < A.ny3;
   unsigned long long* const cnt = A.counters + (b % kCntSlots) * CNT_N;
 
-  // every workgroup reads the mode before it takes its ticket, so the last
-  // one may change it; it and the flag are read again there, not kept
-  // one 64-bit atomic: workgroups done (low half), chunks with a candidate (high)
-  auto leave = [&](bool had) {
+  // Every workgroup reads the mode before it takes its ticket, so the last
+  // one may change it; it and the chunk's record are read again after the
+  // march, not kept.  Tickets are 64-bit atomics (workgroups done in the low
+  // half, chunks with a candidate in the high), taken in groups: a thousand on
+  // one address, after two dependent loads, cost 11 us of a 705 us step
+  // (256^3 FP32).
+  auto leave = [&](bool had, bool dense, bool flagged, unsigned long long pos) {
     if (tid != 0) return;
     // the first kernel's positivity events stand where this one did nothing
     Med3Chunk* const chunk_st = med3_chunk(A.med3) + tb;
-    const bool dense = A.med3->dense != 0, flagged = chunk_st->flag != 0;
-    const unsigned long long pos = chunk_st->pos_events;
     if (pos && !dense && !flagged) atomicAdd(cnt + CNT_POSITIVITY, pos);
     if (pos) chunk_st->pos_events = 0ull;
     if (flagged) chunk_st->flag = 0ull;
+    const int g = tb % kMed3Groups;
     const unsigned long long mine = 1ull | ((had ? 1ull : 0ull) << 32);
-    const unsigned long long all = atomicAdd(&A.med3->tally, mine) + mine;
-    if ((unsigned int)all == (unsigned int)T) {
+    const unsigned long long in_g = atomicAdd(&A.med3->group[g][0], mine) + mine;
+    if ((unsigned int)in_g != (unsigned int)((T - g + kMed3Groups - 1) / kMed3Groups)) return;
+    A.med3->group[g][0] = 0ull;
+    const unsigned long long sum = (in_g & ~0xffffffffull) | 1ull;
+    const unsigned long long all = atomicAdd(&A.med3->tally, sum) + sum;
+    if ((unsigned int)all == (unsigned int)min(T, kMed3Groups)) {
       const unsigned long long held = all >> 32;
       A.med3->dense = dense ? (8 * held >= (unsigned long long)T ? 1 : 0)
                             : (4 * held > (unsigned long long)T ? 1 : 0);
@@ -177,9 +183,12 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     }
   };
   if constexpr (!ALL) {
-    if (!A.med3->dense && !med3_chunk(A.med3)[tb].flag) {
+    // (all three loads before the branch: one round trip)
+    const int dense = A.med3->dense;
+    const unsigned long long flag = med3_chunk(A.med3)[tb].flag, pos = med3_chunk(A.med3)[tb].pos_events;
+    if (!(flag | (unsigned long long)dense)) {
       __syncthreads();   // every wavefront has read the mode: the ticket lets it change
-      leave(false);
+      leave(false, false, false, pos);
       return;
     }
     if (tid == 0) s_had = 0;   // the first layer's barrier is before the first candidate
@@ -251,7 +260,9 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     finish27<S>(A, (unsigned)((z * A.ny3 + y) * A.pitch + x), valid, v, feq, cnt + CNT_POSITIVITY);
     __syncthreads();   // the next layer overwrites the ring slot of z - 1
   }
-  if constexpr (!ALL) leave(s_had != 0);
+  if constexpr (!ALL)
+    leave(s_had != 0, A.med3->dense != 0, med3_chunk(A.med3)[tb].flag != 0,
+          med3_chunk(A.med3)[tb].pos_events);
 }
 
 // ---------------------------------------------------------------------------
