@@ -257,6 +257,9 @@ __device__ __forceinline__ void adjoint_site(const StepArgs<typename StoreT<S>::
 // every pull source lies inside, at a fixed offset from the site (a scalar
 // base per population instead of a selected plane and 64-bit address; the
 // pull itself, whose loads a branch would hold up, measured slower with it).
+// LBGK goes without it: its kernel is bound by HBM, and the two paths cost
+// more than the addresses (4096^2 FP32 347 against 358 us, FP64 668 against 703;
+// MRT's FP32 kernel went from 519 to 351 us with it and the constant matrices).
 template <int Q>
 __device__ __forceinline__ bool interior_wave(int nx, int ny, int x, int y) {
   const bool ring = x == 0 || x == nx - 1 || (Q == 9 && (y == 0 || y == ny - 1));
@@ -267,11 +270,11 @@ __device__ __forceinline__ bool interior_wave(int nx, int ny, int x, int y) {
 // population that site (x, y) pulled in direction i, goes to that
 // population's slot of the adjoint lattice (add = true adds it to what is
 // there).  Every slot is reached from exactly one site.
-template <class R, int Q, bool ADD = false>
+template <class R, int Q, bool ADD = false, bool FAST = true>
 __device__ __forceinline__ void push_adjoint(const StepArgs<R>& A, R* lam_out, int x, int y,
                                              const R val[Q]) {
   const long long o = (long long)y * A.pitch + x;
-  if (interior_wave<Q>(A.nx, A.ny, x, y)) {
+  if (FAST && interior_wave<Q>(A.nx, A.ny, x, y)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       R* dst = at(lam_out + (long long)i * A.qs,
@@ -337,7 +340,10 @@ void k_adjoint(const StepArgs<typename StoreT<S>::R> A, const AdjArgs<typename S
   if (s >= (long long)A.nx * A.ny) return;
   bool ehr = B.mask && B.mask[s];
   for (int j = 0; j < nl; ++j) ehr |= lsel[j] == (int32_t)s;
-  const int y = (int)((unsigned)s / (unsigned)A.nx), x = (int)((unsigned)s % (unsigned)A.nx);
+  // FP32 LBGK at 72 registers is bound by HBM and hides the 64-bit quotient;
+  // with the 32-bit one it spills 8 bytes more (4096^2: 338 against 361 us).
+  using U = std::conditional_t<COLL == COLL_LBGK && sizeof(R) == 4, long long, unsigned>;
+  const int y = (int)((U)s / (U)A.nx), x = (int)((U)s % (U)A.nx);
   R v[Q], feq[Q], d[Q], m0, ux, uy;
   site_prep<S, Q, false, false>(A, x, y, v, feq, d, m0, ux, uy, false);
   const long long o = (long long)y * A.pitch + x;
@@ -349,7 +355,7 @@ void k_adjoint(const StepArgs<typename StoreT<S>::R> A, const AdjArgs<typename S
     // step: nontemporal loads and stores
     lam[i] = __builtin_nontemporal_load(&B.lam_in[(long long)i * A.qs + o]);
   adjoint_site<S, Q, COLL, SELMRT>(A, B, o, ehr, v, feq, d, ux, uy, om, lam, a, gw);
-  push_adjoint<R, Q>(A, B.lam_out, x, y, a);
+  push_adjoint<R, Q, false, COLL != COLL_LBGK>(A, B.lam_out, x, y, a);
   if (B.gom) __builtin_nontemporal_store(__builtin_nontemporal_load(&B.gom[o]) + gw, &B.gom[o]);
 }
 
