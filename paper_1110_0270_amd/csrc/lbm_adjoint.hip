@@ -669,7 +669,7 @@ hipError_t launch_adjoint(int storage, int Q, int coll, const void* step_args, c
 
 // The recompute's step with the recorded Ehrenfest sites (a list short enough
 // for LDS) sent to f* at once: no entropy, no candidates, no counters, and no
-// second launch for the list.  512^2 MRT FP32: 7.6 + 3.5 -> 7.7 us a step.
+// second launch for the list.  512^2 MRT FP32: 7.6 + 3.5 -> 6.5 us a step.
 template <class S, int Q, int COLL>
 __global__ __launch_bounds__(256) void k_restep(const StepArgs<typename StoreT<S>::R> A,
                                                 const int32_t* list, const long long* count,
