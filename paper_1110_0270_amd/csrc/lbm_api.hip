@@ -41,6 +41,7 @@ struct Layout {
   int rows = 0;            // ny, or nz * ny for D3Q27
   size_t off_nl = 0;       // nonlocal filter coefficients (27 values of the compute type)
   size_t clear_bytes = 0;  // lbm_step_noalloc: the clear part at the front
+  size_t need = 0;         // lbm_step_noalloc: what is compared with the array's size
   size_t off_med3 = 0, med3_bytes = 0;  // D3Q27 median step: Med3State and the chunk records
   size_t off_lat[2] = {0, 0}, off_omega = 0, off_sel = 0, off_cnt = 0, off_partial = 0,
          off_stats = 0, off_div = 0, off_ckey = 0, off_cidx = 0, off_cmom = 0, off_hist = 0,
@@ -213,6 +214,17 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
     o = L.adj.end;
   }
   L.total = o;
+  if (!lattices) {
+    // The limit counts the buffers that a context with this configuration has
+    // beside its lattices, statistics included: the fixed front, which a
+    // configuration may not use in full, does not move it.
+    const bool ehr = (c->limiters & LBM_LIM_EHRENFEST) != 0;
+    const bool f64_list = c->collision == LBM_ELBM && !is_f64(c->storage);
+    const size_t front = L.clear_bytes - align256(sizeof(SelState));
+    const size_t cnt = align256(2 * sizeof(unsigned int));
+    L.need = o - (ehr ? 0 : front - cnt) - (f64_list ? 0 : cnt) +
+             align256(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
+  }
   return L;
 }
 
@@ -1087,9 +1099,9 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
   if (cfg->lattice == LBM_D3Q27 || cfg->nl_filter)
     return fail(LBM_EUNSUPPORTED, "lbm_step_noalloc covers the D1Q3 and D2Q9 steps without the nonlocal filter");
   const Layout L = make_layout(cfg, false);
-  if (L.total > (size_t)LBM_NOALLOC_SCRATCH_BYTES)
+  if (std::max(L.need, L.total) > (size_t)LBM_NOALLOC_SCRATCH_BYTES)
     return fail(LBM_EWORKSPACE, "lbm_step_noalloc: this configuration needs " +
-                                    std::to_string(L.total) + " bytes of scratch, above the " +
+                                    std::to_string(L.need) + " bytes of scratch, above the " +
                                     std::to_string((long long)LBM_NOALLOC_SCRATCH_BYTES) +
                                     "-byte static array (use lbm_init with a workspace)");
   int dev = 0;
