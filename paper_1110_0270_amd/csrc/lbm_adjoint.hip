@@ -269,12 +269,14 @@ __device__ __forceinline__ bool interior_wave(int nx, int ny, int x, int y) {
 // Transpose of the pull: val_i, the derivative with respect to the
 // population that site (x, y) pulled in direction i, goes to that
 // population's slot of the adjoint lattice (add = true adds it to what is
-// there).  Every slot is reached from exactly one site.
+// there).  Every slot is reached from exactly one site.  The interior path's
+// 32-bit offsets serve planes of up to 4 GiB; larger ones take the general
+// path's 64-bit addresses.
 template <class R, int Q, bool ADD = false, bool FAST = true>
 __device__ __forceinline__ void push_adjoint(const StepArgs<R>& A, R* lam_out, int x, int y,
                                              const R val[Q]) {
   const long long o = (long long)y * A.pitch + x;
-  if (FAST && interior_wave<Q>(A.nx, A.ny, x, y)) {
+  if (FAST && offsets_fit<R>(A.qs) && interior_wave<Q>(A.nx, A.ny, x, y)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       R* dst = at(lam_out + (long long)i * A.qs,

@@ -92,6 +92,14 @@ __device__ __forceinline__ S* at(S* base, unsigned off) {
   return (S*)((char*)base + off * (unsigned)sizeof(S));
 }
 
+// Whether at()'s 32-bit byte offsets reach every one of `elems` elements of T.
+// (The adjoint lattice is FP32 or FP64 for every storage form, so its planes
+// pass 4 GiB at half the sites that a 16-bit lattice's do.)
+template <class T>
+__host__ __device__ constexpr bool offsets_fit(long long elems) {
+  return elems <= (1ll << 32) / (long long)sizeof(T);
+}
+
 // Pull on a periodic lattice, branch-free: three source rows and three source
 // columns per site, each population at a scalar base plus a 32-bit offset.
 // CACHED: cached loads (the caller reads some populations twice).
