@@ -238,15 +238,6 @@ template <> __device__ __forceinline__ float r_inf<float>() { return __builtin_h
 //   S_f'  = -sum D_i ln((f_i + alpha D_i) / f*_i)
 //   S_f'' = -sum D_i^2 / (f_i + alpha D_i)
 // ---------------------------------------------------------------------------
-// x = num / f: in FP32 num times rf = rcp(f), the value fdiv gives, with the
-// reciprocal taken once per site instead of once per evaluation; in FP64 the
-// correctly rounded quotient.
-template <class R>
-__device__ __forceinline__ R over_f(R num, R f, R rf) {
-  if constexpr (sizeof(R) == 4) return num * rf;
-  else return num / f;
-}
-
 // True when b holds on every active lane of the wavefront.
 __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 
@@ -259,6 +250,10 @@ __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 // computed |x_i| = |fl(fl(a D_i) rf_i)| < 0.1 (the margin of 1e-6 covers
 // the two roundings), so that the wavefront can take the series alone;
 // below 2^-8 it takes their first terms.
+// x_i = a D_i / f_i: in FP32 a D_i times rf_i = rcp(f_i), the value fdiv
+// gives, with the reciprocal taken once per site instead of once per
+// evaluation; in FP64 the correctly rounded quotient, and rf is not read (it
+// may be null).
 // SHORT (FP32): the kernel expects resolved flows and carries the short
 // series.
 template <class R> struct ElbmSeries { static constexpr int T = sizeof(R) == 4 ? 3 : 10; };
@@ -270,6 +265,10 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
 #pragma unroll
   for (int n = 0; n < NT; ++n) T[n] = R(0);
   rmax = R(0);
+  auto x_of = [&](int i) {
+    if constexpr (sizeof(R) == 4) return a * D[i] * rf[i];
+    else return a * D[i] / f[i];
+  };
   auto higher = [&](int i) {
     if constexpr (sizeof(R) == 4) {
       const R r = D[i] * rcp<R>(f[i] + a * D[i]);
@@ -292,7 +291,7 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
   if (SHORT && wave_all(a * m < R(kShortSeries))) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const R x = over_f<R>(a * D[i], f[i], rf[i]);
+      const R x = x_of(i);
       s0 += f[i] * ((R)h_poly_short((float)x) * x * x);
       t1 += D[i] * (R)lg1p_series_short((float)x);
       higher(i);
@@ -302,7 +301,7 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
     // series, the values the selects below would keep
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const R x = over_f<R>(a * D[i], f[i], rf[i]);
+      const R x = x_of(i);
       s0 += f[i] * h_series<R>(x);
       t1 += D[i] * lg1p_series<R>(x);
       higher(i);
@@ -310,7 +309,7 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
   } else {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      const R x = over_f<R>(a * D[i], f[i], rf[i]);
+      const R x = x_of(i);
       const R xl = x < R(-1) ? R(-1) : x;
       const R l = lg1p<R>(xl);
       s0 += f[i] * h_log<R>(x, l);
@@ -352,7 +351,7 @@ struct ElbmParams {
 // inequality), so sum f*_i x_i^2 / (2 (1 + max x/3)) <= Delta S decides it
 // for every other site.  The same x_i give ln(f_i / f*_i) and the entropic
 // norm.
-// FP32: rf = rcp(f), m = max_i |D_i| / f_i.  `lower` says that amax is only a
+// FP32: rf = rcp(f), m = max_i |D_i| / f_i (FP64 reads neither).  `lower` says that amax is only a
 // lower bound of alpha_max; the exact value is taken where the bound does not
 // settle a decision (the decisions, and so alpha, are those of the exact one).
 template <class R, int Q, bool SHORT = false>
