@@ -432,7 +432,7 @@ __device__ __forceinline__ void site_finish(const StepArgs<typename StoreT<S>::R
       unsigned int base = 0;
       if (lane == leader) base = atomicAdd(A.f64_count, (unsigned int)__popcll(m));
       base = __shfl(base, leader);
-      if (deferred) A.f64_sites[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)(y * A.nx + x);
+      if (deferred) A.f64_sites[base + lanes_below(m)] = (uint32_t)(y * A.nx + x);
     }
   }
 }

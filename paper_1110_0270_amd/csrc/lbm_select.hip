@@ -348,7 +348,7 @@ __device__ void append_sites(const StepArgs<typename StoreT<S>::R>& A, int wg, i
     }
     const typename KeyOf<R>::T key = key_of<R>(dS);
     if (is_c) {
-      const long long pos = region * 64 + __popcll(mask & ((1ull << lane) - 1ull));
+      const long long pos = region * 64 + lanes_below(mask);
       st_dev(&A.cand_key[pos], key);
       st_dev(&A.cand_idx[pos], (uint32_t)(y * A.nx + x));
       st_dev(&A.cand_mom[pos], m0);
@@ -396,7 +396,7 @@ __device__ __forceinline__ unsigned int lds_slot(bool on, unsigned int* ctr) {
   unsigned int base = 0;
   if (lane == leader) base = atomicAdd(ctr, (unsigned int)__popcll(mask));
   base = __shfl(base, leader);
-  return base + (unsigned int)__popcll(mask & ((1ull << lane) - 1ull));
+  return base + lanes_below(mask);
 }
 
 // Boundary-bucket entries that the exact resolution stages in LDS; lists of

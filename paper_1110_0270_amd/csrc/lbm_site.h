@@ -478,7 +478,7 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
     atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
   }
   if (is_c) {
-    const long long pos = region * 64 + __popcll(mask & ((1ull << lane) - 1ull));
+    const long long pos = region * 64 + lanes_below(mask);
     A.cand_key[pos] = key;
     A.cand_idx[pos] = idx;
     A.cand_mom[pos] = m0;

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const StepArgs<typename
       if (lane == leader) base = atomicAdd(&s_nc, (unsigned int)__popcll(mask));
       base = __shfl(base, leader);
       if (is_c) {
-        const unsigned int q = base + (unsigned int)__popcll(mask & ((1ull << lane) - 1ull));
+        const unsigned int q = base + lanes_below(mask);
         c_key[q] = key;
         c_site[q] = (uint16_t)x;
       }
