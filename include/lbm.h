@@ -327,8 +327,8 @@ lbm_status lbm_profile_backward(lbm_ctx* ctx, const void* dL_dfT, void* dL_df0,
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): one time
- * step exactly as lbm_step takes it (same kernels), from the lattice f_src
- * into the lattice f_dst, allocating nothing.  Every other buffer of the
+ * step exactly as lbm_step takes it (the same site arithmetic, so the same
+ * bits), from the lattice f_src into the lattice f_dst, allocating nothing.  Every other buffer of the
  * step (selection state, Ehrenfest candidates and lists, histograms, limiter
  * counters, the FP64-solve list) lives in a static device array of
  * LBM_NOALLOC_SCRATCH_BYTES that each device holds until the process ends.
@@ -341,7 +341,8 @@ lbm_status lbm_profile_backward(lbm_ctx* ctx, const void* dL_dfT, void* dL_df0,
  *   stream: a hipStream_t (NULL = default stream); the call only enqueues.
  * Each call starts the Ehrenfest selection from its threshold (no candidate
  * floor is carried between calls), so it examines every eligible site.
- * The limiter events are not counted.
+ * No call takes anything from what earlier calls left in the array, also not
+ * a captured call that is replayed.  The limiter events are not counted.
  * Errors: LBM_EINVAL (configuration, NULL or equal buffers), LBM_EWORKSPACE
  * when the configuration needs more scratch than the array holds (large
  * lattices with the Ehrenfest limiter or FP32 ELBM: use lbm_init with a

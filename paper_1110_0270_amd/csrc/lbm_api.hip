@@ -40,8 +40,6 @@ struct Layout {
   size_t lat_bytes = 0;
   int rows = 0;            // ny, or nz * ny for D3Q27
   size_t off_nl = 0;       // nonlocal filter coefficients (27 values of the compute type)
-  size_t clear_bytes = 0;  // lbm_step_noalloc: the clear part at the front
-  size_t need = 0;         // lbm_step_noalloc: what is compared with the array's size
   size_t off_med3 = 0, med3_bytes = 0;  // D3Q27 median step: Med3State and the chunk records
   size_t off_lat[2] = {0, 0}, off_omega = 0, off_sel = 0, off_cnt = 0, off_partial = 0,
          off_stats = 0, off_div = 0, off_ckey = 0, off_cidx = 0, off_cmom = 0, off_hist = 0,
@@ -160,17 +158,8 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
   }
   L.off_omega = c->omega_field ? take((size_t)L.qs * rb) : 0;
   L.off_sel = take(sizeof(SelState));
-  if (!lattices) {
-    // lbm_step_noalloc: what a step expects clear lies at the same place for
-    // every configuration, where the previous call left it clear
-    L.off_hist = take((size_t)kHistWords * 4);
-    L.off_coarse = take(kCoarse * 4);
-    L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
-    L.off_f64cnt = take(2 * sizeof(unsigned int));
-    L.clear_bytes = o;
-  }
   L.off_cnt = take((size_t)kCntSlots * CNT_N * sizeof(unsigned long long));
-  if (lattices) L.off_partial = take(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
+  L.off_partial = take(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
   L.off_nl = c->nl_filter ? take(27 * rb) : 0;
   if (L.Q == 27 && (c->limiters & LBM_LIM_MEDIAN)) {
     L.med3_bytes = sizeof(Med3State) + (size_t)med3_chunks(c->storage, c->nx, c->ny, c->nz) * sizeof(Med3Chunk);
@@ -188,11 +177,9 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
     L.off_cidx = take((size_t)L.cap * 4);
     L.off_cmom = take((size_t)L.cap * 3 * rb);
     L.off_wcount = take((size_t)tiles * 4 * 4);
-    if (lattices) {
-      L.off_hist = take((size_t)kHistWords * 4);
-      L.off_coarse = take(kCoarse * 4);
-      L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
-    }
+    L.off_hist = take((size_t)kHistWords * 4);
+    L.off_coarse = take(kCoarse * 4);
+    L.off_ccount = take((size_t)kCountSlots * kCountStride * 8);
     // kSweepRegions regions x 64 entries per sweep workgroup
     L.off_stage = take((size_t)((tiles * 4 + kSweepRegions - 1) / kSweepRegions) * kSweepRegions * 64 * 4);
     L.bcap = std::min<long long>(L.cap, 1ll << 20);
@@ -201,7 +188,7 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
   }
   if (c->collision == LBM_ELBM && !is_f64(c->storage)) {
     L.off_f64list = take((size_t)L.n_sites * 4);
-    if (lattices) L.off_f64cnt = take(2 * sizeof(unsigned int));
+    L.off_f64cnt = take(2 * sizeof(unsigned int));
   }
   if (c->ens_limiter != LBM_ENS_NONE) {
     L.off_ens = take(sizeof(EnsState));
@@ -214,17 +201,6 @@ Layout make_layout(const lbm_config* c, bool lattices = true) {
     o = L.adj.end;
   }
   L.total = o;
-  if (!lattices) {
-    // The limit counts the buffers that a context with this configuration has
-    // beside its lattices, statistics included: the fixed front, which a
-    // configuration may not use in full, does not move it.
-    const bool ehr = (c->limiters & LBM_LIM_EHRENFEST) != 0;
-    const bool f64_list = c->collision == LBM_ELBM && !is_f64(c->storage);
-    const size_t front = L.clear_bytes - align256(sizeof(SelState));
-    const size_t cnt = align256(2 * sizeof(unsigned int));
-    L.need = o - (ehr ? 0 : front - cnt) - (f64_list ? 0 : cnt) +
-             align256(stats_partial_doubles(c->nx, L.rows) * sizeof(double));
-  }
   return L;
 }
 
@@ -1058,6 +1034,10 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
+}  // namespace
+
+namespace lbm {
+// Device address of `scratch` on the current device `dev`.
 hipError_t scratch_address(int dev, void** out) {
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   if (!g_scratch_ptr[dev]) {
@@ -1070,19 +1050,24 @@ hipError_t scratch_address(int dev, void** out) {
   *out = g_scratch_ptr[dev];
   return hipSuccess;
 }
+}  // namespace lbm
 
-// The front of the scratch array (selection state, histograms, candidate
-// counters, the FP64 site list's count) is clear between calls: it is when the
-// library is loaded (static device memory), and a call's last kernel leaves it
-// so, whatever it found.  Only a call that failed to enqueue all its kernels
-// may not have: the next one clears it with a kernel first (no memset nodes
-// when the caller captures the call), and one that is being captured leaves
-// that to the next call outside a capture as well.
-bool g_scratch_dirty[kMaxDevices] = {};
+namespace {
 
-__global__ void k_scratch_clear(uint4* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    p[i] = make_uint4(0u, 0u, 0u, 0u);
+// What a step's kernels add to before anything of the step has written it,
+// cleared by a kernel (no memset nodes when the caller captures the call).
+// Nothing in the array is taken from an earlier call, so a call is right
+// whatever is there: after a call of another configuration, after one that
+// failed between its launches, and when a captured call is replayed.
+struct ScratchClear {
+  uint32_t* p[3];
+  int words[3];
+};
+
+__global__ void k_scratch_clear(const ScratchClear r) {
+  for (int j = 0; j < 3; ++j)
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < r.words[j]; i += gridDim.x * blockDim.x)
+      r.p[j][i] = 0u;
 }
 
 }  // namespace
@@ -1099,9 +1084,9 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
   if (cfg->lattice == LBM_D3Q27 || cfg->nl_filter)
     return fail(LBM_EUNSUPPORTED, "lbm_step_noalloc covers the D1Q3 and D2Q9 steps without the nonlocal filter");
   const Layout L = make_layout(cfg, false);
-  if (std::max(L.need, L.total) > (size_t)LBM_NOALLOC_SCRATCH_BYTES)
+  if (L.total > (size_t)LBM_NOALLOC_SCRATCH_BYTES)
     return fail(LBM_EWORKSPACE, "lbm_step_noalloc: this configuration needs " +
-                                    std::to_string(L.need) + " bytes of scratch, above the " +
+                                    std::to_string(L.total) + " bytes of scratch, above the " +
                                     std::to_string((long long)LBM_NOALLOC_SCRATCH_BYTES) +
                                     "-byte static array (use lbm_init with a workspace)");
   int dev = 0;
@@ -1130,21 +1115,22 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
   }
   const bool ehr = (cfg->limiters & LBM_LIM_EHRENFEST) != 0;
   // no counters are reported, and no floor is carried from call to call
-  a64.no_carry = a32.no_carry = 1;
+  const bool regions = ehr && select_chunks(L.cap / 256) == 1;
+  a64.no_carry = a32.no_carry = regions ? NO_CARRY_REGIONS : NO_CARRY;
   a64.count_events = a32.count_events = 0;
-  bool was_dirty;
-  {
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    was_dirty = g_scratch_dirty[dev];
-    g_scratch_dirty[dev] = true;
+  ScratchClear r = {};
+  if (ehr && !regions) {
+    r.p[0] = (uint32_t*)(ws + L.off_sel);
+    r.words[0] = (int)(sizeof(SelState) / 4);
+    r.p[1] = (uint32_t*)(ws + L.off_hist);   // and the coarse histogram and counters behind it
+    r.words[1] = (int)((L.off_ccount - L.off_hist) / 4) + kCountSlots * kCountStride * 2;
   }
-  bool stays_dirty = false;
-  if (was_dirty) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    e = hipStreamIsCapturing(st, &cs);
-    if (e != hipSuccess) return hip_fail(e, "lbm_step_noalloc");
-    stays_dirty = cs != hipStreamCaptureStatusNone;
-    hipLaunchKernelGGL(k_scratch_clear, dim3(8), dim3(256), 0, st, (uint4*)ws, (int)(L.clear_bytes / 16));
+  if (L.off_f64cnt) {
+    r.p[2] = (uint32_t*)(ws + L.off_f64cnt);
+    r.words[2] = 2;
+  }
+  if (r.words[0] + r.words[2] > 0) {
+    hipLaunchKernelGGL(k_scratch_clear, dim3(32), dim3(256), 0, st, r);
     e = hipGetLastError();
   }
   if (e == hipSuccess)
@@ -1166,10 +1152,6 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
     e = launch_select(sa, st);
   }
   if (e != hipSuccess) return hip_fail(e, "lbm_step_noalloc");
-  if (!stays_dirty) {
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    g_scratch_dirty[dev] = false;
-  }
   return LBM_OK;
 }
 

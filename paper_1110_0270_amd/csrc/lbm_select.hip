@@ -417,8 +417,9 @@ union SelScratch {
 };
 
 // Exact resolution of the boundary bucket and the next step's floor and
-// frame, by one workgroup.
-template <class S, int Q>
+// frame, by one workgroup.  CARRY false (NO_CARRY_REGIONS): leaves neither
+// floor nor frame, and the histogram and counters are not in use.
+template <class S, int Q, bool CARRY>
 __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, long long n_sites,
                          int32_t* selected, uint32_t* blist, long long bcap,
                          long long* n_sel_out, int32_t* tape_sel, long long* tape_cnt,
@@ -445,7 +446,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   const unsigned long long b_above = bd.above;
   const long long m_all = (long long)(sel_bnd & 0xffffffffull);
   // state the epilogue updates
-  const bool fell_back = st->fallback != 0;
+  const bool fell_back = CARRY && st->fallback != 0;
   const long long tape_t = st->tape_t;
   if (tape_sel && tape_t < tape_len) {
     selected = tape_sel + tape_t * k;
@@ -727,7 +728,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   // current candidates' range above the floor.
   const unsigned long long dk = delta_key<R>(A.ehr_delta);
   unsigned long long fnext = dk;
-  if (10 * k < n_sites && k > 0) {
+  if (CARRY && 10 * k < n_sites && k > 0) {
     const bool keep = raised && !fell_back && nc >= 2 * k && nc <= 7 * k / 2;
     if (keep) {
       fnext = floor_prev;
@@ -749,7 +750,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
   __shared__ int s_top;
   if (threadIdx.x == 0) s_top = -1;
   __syncthreads();
-  {
+  if constexpr (CARRY) {
     int tmax = -1;
     for (int i = threadIdx.x; i < kBuckets; i += blockDim.x)
       if (h[hx(i)]) tmax = i;
@@ -767,7 +768,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     const unsigned long long span = (unsigned long long)kBuckets << shift;
     const unsigned long long hi_key = s_top < 0 ? fnext + 1
         : (s_top < kBuckets - 1 ? base + ((unsigned long long)(s_top + 1) << shift) : base + 2 * span);
-    if (!A.no_carry) {
+    if (CARRY && !A.no_carry) {
       st->floor_key[par] = fnext;
       st->floor_raised[par] = fnext > dk ? 1 : 0;
       // (a floor at the threshold 0 would spread the frame over every octave
@@ -787,6 +788,7 @@ __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, 
     st->step += 1;
     st->tape_t = tape_t + 1;
   }
+  if constexpr (!CARRY) return;
   for (int i = threadIdx.x; i < kHistWords; i += blockDim.x) A.hist[i] = 0;
   for (int i = threadIdx.x; i < kCountSlots; i += blockDim.x) A.ccount[i * kCountStride] = 0;
 }
@@ -997,14 +999,14 @@ __device__ unsigned long long sweep_all(const StepArgs<typename StoreT<S>::R>& A
   return ((unsigned long long)s_sel << 32) | s_bnd;
 }
 
-template <class S, int Q>
+template <class S, int Q, bool CARRY = true>
 __device__ __forceinline__ void tail_of(const StepArgs<typename StoreT<S>::R>& A, const TailArgs& a,
                                         const Boundary& bd, const StepFrame& fr,
                                         unsigned long long sel_bnd,
                                         unsigned int* h, bool have_h, SelScratch& lds) {
   // the region sweep's stage (one entry per candidate slot) serves as the
   // exact resolution's scratch
-  fix_tail<S, Q>(A, a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
+  fix_tail<S, Q, CARRY>(A, a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
                  a.tape_cnt, a.tape_len, (uint32_t*)a.stage,
                  (long long)a.nchunk * kSweepRegions * 64, bd, fr, sel_bnd, h, have_h, lds);
 }
@@ -1076,36 +1078,77 @@ __global__ __launch_bounds__(1024) void k_sel_tail(const StepArgs<typename Store
   tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, fallback != 0, lds);
 }
 
-// The whole selection of a small lattice by one workgroup.
-template <class S, int Q>
+// The histogram (into LDS) and the count of an uncarried step's candidates,
+// from the regions themselves: one wavefront per region, eight regions' loads
+// in flight.  So lbm_step_noalloc needs nothing clear before its step kernel
+// and no launch to clear it.
+template <class R>
+__device__ __forceinline__ long long count_regions(const StepArgs<R>& A, const StepFrame& fr, unsigned int* h) {
+  __shared__ unsigned int s_n;
+  for (int i = threadIdx.x; i < kHistLds; i += blockDim.x) h[i] = 0;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  constexpr int U = 8;
+  const int nreg = A.tiles_x * A.tiles_y * 4;
+  const int w = threadIdx.x / 64, lane = threadIdx.x % 64, nw = (int)blockDim.x / 64;
+  unsigned int n = 0;
+  for (int r0 = w; r0 < nreg; r0 += U * nw) {
+    uint32_t cnt[U];
+    unsigned long long key[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cnt[u] = r0 + u * nw < nreg ? A.wcount[r0 + u * nw] : 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      key[u] = (uint32_t)lane < cnt[u] ? (unsigned long long)A.cand_key[(long long)(r0 + u * nw) * 64 + lane] : 0ull;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      n += cnt[u];
+      hist_add(h, (unsigned int)hx(bucket_of<R>(key[u], fr.base, fr.shift)), (uint32_t)lane < cnt[u]);
+    }
+  }
+  if (lane == 0 && n) atomicAdd(&s_n, n);
+  __syncthreads();
+  return (long long)s_n;
+}
+
+// The whole selection of a small lattice by one workgroup; CARRY false: of a
+// step that takes nothing from the one before (no floor, so no rescan).
+template <class S, int Q, bool CARRY>
 __global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT<S>::R> A,
                                                   const TailArgs a) {
   using R = typename StoreT<S>::R;
   SelState* st = A.sel;
   __shared__ unsigned int h[kHistLds];
   __shared__ SelScratch lds;
-  const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
-  const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
-  StepFrame fr = step_frame<R>(A);
   int32_t* selected = selected_slot(a, st);
-  long long nc = load_counts<R>(A, h);
-  if (nc < a.k && raised) {
-    __syncthreads();
-    scan_sites<S, Q>(A, h, a.coarse, 0, 1);
-    __threadfence();
-    __syncthreads();
-    pick_floor_bin<R>(A, a.k, h, a.coarse, false);
-    __threadfence();
-    __syncthreads();
-    append_sites<S, Q>(A, 0, 1);
-    __threadfence();
-    __syncthreads();
+  long long nc;
+  StepFrame fr;
+  if constexpr (CARRY) {
+    const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
+    const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
     fr = step_frame<R>(A);
     nc = load_counts<R>(A, h);
+    if (nc < a.k && raised) {
+      __syncthreads();
+      scan_sites<S, Q>(A, h, a.coarse, 0, 1);
+      __threadfence();
+      __syncthreads();
+      pick_floor_bin<R>(A, a.k, h, a.coarse, false);
+      __threadfence();
+      __syncthreads();
+      append_sites<S, Q>(A, 0, 1);
+      __threadfence();
+      __syncthreads();
+      fr = step_frame<R>(A);
+      nc = load_counts<R>(A, h);
+    }
+  } else {
+    fr = StepFrame{0ull, FirstFrame<R>::base, FirstFrame<R>::shift};
+    nc = count_regions<R>(A, fr, h);
   }
   const Boundary bd = boundary_from(h, nc, a.k);
   const unsigned long long sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected);
-  tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, true, lds);
+  tail_of<S, Q, CARRY>(A, a, bd, fr, sel_bnd, h, true, lds);
 }
 
 // The MRT limiter (section 5) on an LBGK lattice: the step's selected sites,
@@ -1140,11 +1183,12 @@ static hipError_t launch_select_t(const SelectArgs& a, hipStream_t s) {
   using R = typename StoreT<S>::R;
   const StepArgs<R>& A = *(const StepArgs<R>*)a.step_args;
   const long long tiles = (long long)A.tiles_x * A.tiles_y;
-  const int nchunk = (int)((tiles * 4 + kSweepRegions - 1) / kSweepRegions);
+  const int nchunk = select_chunks(tiles);
   const TailArgs t{a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
                    a.tape_cnt, a.tape_len, a.segsel, a.coarse, nchunk};
   if (nchunk == 1) {
-    hipLaunchKernelGGL((k_sel_one<S, Q>), dim3(1), dim3(1024), 0, s, A, t);
+    auto one = A.no_carry == NO_CARRY_REGIONS ? k_sel_one<S, Q, false> : k_sel_one<S, Q, true>;
+    hipLaunchKernelGGL(one, dim3(1), dim3(1024), 0, s, A, t);
   } else {
     // one workgroup per chunk of regions; a rescan (rare) takes at least a
     // workgroup per CU of a lattice that has the tiles for them

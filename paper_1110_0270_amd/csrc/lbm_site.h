@@ -468,14 +468,16 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
                                                   R m0, R ux, R uy) {
   const unsigned long long mask = __ballot(is_c);
   const int lane = __lane_id();
-  // (the counts of a carried selection are left clear by the previous step;
-  // stacked tiles may reach past the last region)
+  // (the counts of a carried selection are left clear by the previous step,
+  // those of an uncarried one are all written here; stacked tiles may reach
+  // past the last region)
   if (A.no_carry && !mask && lane == 0 && region < (long long)A.tiles_x * A.tiles_y * 4)
     A.wcount[region] = 0u;
   if (!mask) return;
+  const bool counts = A.no_carry != NO_CARRY_REGIONS;
   if (lane == __ffsll((long long)mask) - 1) {
     A.wcount[region] = (uint32_t)__popcll(mask);
-    atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
+    if (counts) atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
   }
   if (is_c) {
     const long long pos = region * 64 + lanes_below(mask);
@@ -485,7 +487,8 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
     A.cand_mom[A.cap + pos] = ux;
     A.cand_mom[2 * A.cap + pos] = uy;
   }
-  hist_add(A.hist, (unsigned int)hist_pos(bucket_of<R>((unsigned long long)key, fr.base, fr.shift)), is_c);
+  if (counts)
+    hist_add(A.hist, (unsigned int)hist_pos(bucket_of<R>((unsigned long long)key, fr.base, fr.shift)), is_c);
 }
 
 template <class S, int Q, bool CACHED = false>
