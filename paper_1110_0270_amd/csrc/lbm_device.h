@@ -32,17 +32,20 @@ enum Coll : int { COLL_LBGK = 0, COLL_MRT = 1, COLL_ELBM = 2 };
 enum EqKind : int { EQ_POLY = 0, EQ_ENTROPIC = 1 };
 enum ElbmBranch : int { EB_ROOT = 0, EB_CUTOFF = 1, EB_NOROOT = 2, EB_NONPOS = 3, EB_F64 = 4 };
 
-// Lanes of `mask` below the calling lane.  Counted by v_mbcnt, not as
-// popcount(mask & ((1 << lane) - 1)): a 64-bit shift takes its amount wrongly
-// on gfx950 when that lies in the last vector register of the wavefront's
-// allocation (v127 of 128, v63 of 64; about 15 % of 5e8 shifts by the lane
-// index, none from the register before it), and the compiler does put it
-// there.  A one-workgroup selection that spilled did: every lane of some
-// wavefronts took rank 0, and the list lost 63 of their 64 entries.
-// tests/test_shift64.py looks for the form in the built library.
+// Lanes of `mask` below the calling lane, from 32-bit shifts: a 64-bit shift
+// takes its amount wrongly on gfx950 when that lies in the last vector register
+// of the wavefront's allocation (v127 of 128, v63 of 64; about 15 % of 5e8
+// shifts by the lane index, none from the register before it), and the compiler
+// does put it there.  A one-workgroup selection that spilled did: every lane of
+// some wavefronts took rank 0, and the list lost 63 of their 64 entries.
+// tests/test_shift64.py looks for the form in the built library.  (v_mbcnt
+// instead, which the compiler cannot hoist out of the loops, left the FP64
+// selection kernels 10 to 14 spilled registers more: 2 to 3 % of a 256^2 step
+// with long tie lists.)
 __device__ __forceinline__ unsigned int lanes_below(unsigned long long mask) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
+  const unsigned int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const unsigned int lo = l < 32u ? (1u << l) - 1u : ~0u, hi = l < 32u ? 0u : (1u << (l - 32u)) - 1u;
+  return (unsigned int)__popc((unsigned int)mask & lo) + (unsigned int)__popc((unsigned int)(mask >> 32) & hi);
 }
 
 // ---------------------------------------------------------------------------
