@@ -1115,11 +1115,10 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_config* cfg, const void* f_src,
   }
   const bool ehr = (cfg->limiters & LBM_LIM_EHRENFEST) != 0;
   // no counters are reported, and no floor is carried from call to call
-  const bool regions = ehr && select_chunks(L.cap / 256) == 1;
-  a64.no_carry = a32.no_carry = regions ? NO_CARRY_REGIONS : NO_CARRY;
+  a64.no_carry = a32.no_carry = 1;
   a64.count_events = a32.count_events = 0;
   ScratchClear r = {};
-  if (ehr && !regions) {
+  if (ehr) {
     r.p[0] = (uint32_t*)(ws + L.off_sel);
     r.words[0] = (int)(sizeof(SelState) / 4);
     r.p[1] = (uint32_t*)(ws + L.off_hist);   // and the coarse histogram and counters behind it

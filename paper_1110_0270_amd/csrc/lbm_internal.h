@@ -109,13 +109,6 @@ struct Med3Chunk {
 __host__ __device__ inline Med3Chunk* med3_chunk(Med3State* m) { return reinterpret_cast<Med3Chunk*>(m + 1); }
 long long med3_chunks(int storage, int nx, int ny, int nz);
 
-// StepArgs::no_carry (lbm_step_noalloc: nothing is taken from an earlier step)
-enum NoCarry : int {
-  CARRY = 0,        // floor, frame, histogram and counters left by the previous step
-  NO_CARRY = 1,     // the threshold and the first frame; the histogram and counters are clear
-  NO_CARRY_REGIONS = 2  // the same, and the selection counts the regions' entries itself
-};
-
 template <class R> struct KeyOf;
 template <> struct KeyOf<float> { using T = uint32_t; };
 template <> struct KeyOf<double> { using T = unsigned long long; };
@@ -134,7 +127,7 @@ struct StepArgs {
   int positivity;
   int ehrenfest;
   int count_events;
-  int no_carry;          // NoCarry: the selection starts from its threshold
+  int no_carry;          // the selection starts from its threshold, whatever SelState holds
   R rho0;
   R omega;
   const R* omega_field;  // [ny][pitch] or nullptr
@@ -253,9 +246,6 @@ struct SelectArgs {
   long long tape_len;
 };
 hipError_t launch_select(const SelectArgs& a, hipStream_t s);
-// Sweep workgroups of a lattice of so many 256-site tiles (1: the whole
-// selection is one workgroup's).
-inline int select_chunks(long long tiles) { return (int)((tiles * 4 + kSweepRegions - 1) / kSweepRegions); }
 // Place the first candidate floor of a freshly set lattice at the 3k-th
 // largest Delta S of its next step (one rescan).
 hipError_t launch_select_calibrate(const SelectArgs& a, hipStream_t s);

@@ -417,8 +417,8 @@ union SelScratch {
 };
 
 // Exact resolution of the boundary bucket and the next step's floor and
-// frame, by one workgroup.  CARRY false (NO_CARRY_REGIONS): leaves neither
-// floor nor frame, and the histogram and counters are not in use.
+// frame, by one workgroup.  CARRY false: leaves neither floor nor frame, nor
+// the histogram and counters clear.
 template <class S, int Q, bool CARRY>
 __device__ void fix_tail(const StepArgs<typename StoreT<S>::R>& A, long long k, long long n_sites,
                          int32_t* selected, uint32_t* blist, long long bcap,
@@ -1078,39 +1078,6 @@ __global__ __launch_bounds__(1024) void k_sel_tail(const StepArgs<typename Store
   tail_of<S, Q>(A, a, bd, fr, sel_bnd, h, fallback != 0, lds);
 }
 
-// The histogram (into LDS) and the count of an uncarried step's candidates,
-// from the regions themselves: one wavefront per region, eight regions' loads
-// in flight.  So lbm_step_noalloc needs nothing clear before its step kernel
-// and no launch to clear it.
-template <class R>
-__device__ __forceinline__ long long count_regions(const StepArgs<R>& A, const StepFrame& fr, unsigned int* h) {
-  __shared__ unsigned int s_n;
-  for (int i = threadIdx.x; i < kHistLds; i += blockDim.x) h[i] = 0;
-  if (threadIdx.x == 0) s_n = 0;
-  __syncthreads();
-  constexpr int U = 8;
-  const int nreg = A.tiles_x * A.tiles_y * 4;
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64, nw = (int)blockDim.x / 64;
-  unsigned int n = 0;
-  for (int r0 = w; r0 < nreg; r0 += U * nw) {
-    uint32_t cnt[U];
-    unsigned long long key[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) cnt[u] = r0 + u * nw < nreg ? A.wcount[r0 + u * nw] : 0u;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      key[u] = (uint32_t)lane < cnt[u] ? (unsigned long long)A.cand_key[(long long)(r0 + u * nw) * 64 + lane] : 0ull;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      n += cnt[u];
-      hist_add(h, (unsigned int)hx(bucket_of<R>(key[u], fr.base, fr.shift)), (uint32_t)lane < cnt[u]);
-    }
-  }
-  if (lane == 0 && n) atomicAdd(&s_n, n);
-  __syncthreads();
-  return (long long)s_n;
-}
-
 // The whole selection of a small lattice by one workgroup; CARRY false: of a
 // step that takes nothing from the one before (no floor, so no rescan).
 template <class S, int Q, bool CARRY>
@@ -1121,30 +1088,26 @@ __global__ __launch_bounds__(1024) void k_sel_one(const StepArgs<typename StoreT
   __shared__ unsigned int h[kHistLds];
   __shared__ SelScratch lds;
   int32_t* selected = selected_slot(a, st);
-  long long nc;
-  StepFrame fr;
+  StepFrame fr = step_frame<R>(A);
+  bool raised = false;
   if constexpr (CARRY) {
     const int fr0 = st->floor_raised[0], fr1 = st->floor_raised[1];
-    const bool raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
+    raised = ((st->step & 1ull) ? fr1 : fr0) != 0;
+  }
+  long long nc = load_counts<R>(A, h);
+  if (CARRY && nc < a.k && raised) {
+    __syncthreads();
+    scan_sites<S, Q>(A, h, a.coarse, 0, 1);
+    __threadfence();
+    __syncthreads();
+    pick_floor_bin<R>(A, a.k, h, a.coarse, false);
+    __threadfence();
+    __syncthreads();
+    append_sites<S, Q>(A, 0, 1);
+    __threadfence();
+    __syncthreads();
     fr = step_frame<R>(A);
     nc = load_counts<R>(A, h);
-    if (nc < a.k && raised) {
-      __syncthreads();
-      scan_sites<S, Q>(A, h, a.coarse, 0, 1);
-      __threadfence();
-      __syncthreads();
-      pick_floor_bin<R>(A, a.k, h, a.coarse, false);
-      __threadfence();
-      __syncthreads();
-      append_sites<S, Q>(A, 0, 1);
-      __threadfence();
-      __syncthreads();
-      fr = step_frame<R>(A);
-      nc = load_counts<R>(A, h);
-    }
-  } else {
-    fr = StepFrame{0ull, FirstFrame<R>::base, FirstFrame<R>::shift};
-    nc = count_regions<R>(A, fr, h);
   }
   const Boundary bd = boundary_from(h, nc, a.k);
   const unsigned long long sel_bnd = sweep_all<S, Q>(A, a, bd, fr, selected);
@@ -1183,11 +1146,11 @@ static hipError_t launch_select_t(const SelectArgs& a, hipStream_t s) {
   using R = typename StoreT<S>::R;
   const StepArgs<R>& A = *(const StepArgs<R>*)a.step_args;
   const long long tiles = (long long)A.tiles_x * A.tiles_y;
-  const int nchunk = select_chunks(tiles);
+  const int nchunk = (int)((tiles * 4 + kSweepRegions - 1) / kSweepRegions);
   const TailArgs t{a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
                    a.tape_cnt, a.tape_len, a.segsel, a.coarse, nchunk};
   if (nchunk == 1) {
-    auto one = A.no_carry == NO_CARRY_REGIONS ? k_sel_one<S, Q, false> : k_sel_one<S, Q, true>;
+    auto one = A.no_carry ? k_sel_one<S, Q, false> : k_sel_one<S, Q, true>;
     hipLaunchKernelGGL(one, dim3(1), dim3(1024), 0, s, A, t);
   } else {
     // one workgroup per chunk of regions; a rescan (rare) takes at least a

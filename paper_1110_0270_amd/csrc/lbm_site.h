@@ -474,10 +474,9 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
   if (A.no_carry && !mask && lane == 0 && region < (long long)A.tiles_x * A.tiles_y * 4)
     A.wcount[region] = 0u;
   if (!mask) return;
-  const bool counts = A.no_carry != NO_CARRY_REGIONS;
   if (lane == __ffsll((long long)mask) - 1) {
     A.wcount[region] = (uint32_t)__popcll(mask);
-    if (counts) atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
+    atomicAdd(&A.ccount[(region & (kCountSlots - 1)) * kCountStride], (unsigned long long)__popcll(mask));
   }
   if (is_c) {
     const long long pos = region * 64 + lanes_below(mask);
@@ -487,8 +486,7 @@ __device__ __forceinline__ void append_candidates(const StepArgs<R>& A, const St
     A.cand_mom[A.cap + pos] = ux;
     A.cand_mom[2 * A.cap + pos] = uy;
   }
-  if (counts)
-    hist_add(A.hist, (unsigned int)hist_pos(bucket_of<R>((unsigned long long)key, fr.base, fr.shift)), is_c);
+  hist_add(A.hist, (unsigned int)hist_pos(bucket_of<R>((unsigned long long)key, fr.base, fr.shift)), is_c);
 }
 
 template <class S, int Q, bool CACHED = false>
