@@ -21,8 +21,8 @@
 //               the next step's floor and frame, and resets the counters.
 //               After a rescan its workgroups first append the sites from
 //               the floor bin up, and the last of them sweeps all regions;
-//   k_sel_one   lattices of one sweep workgroup (65536 sites at most): all of
-//               it in one launch of one workgroup;
+//   k_sel_one   small lattices (select_one): all of it in one launch of one
+//               workgroup;
 //   k_sel_mrt   (MRT limiter only) replaces f* at the selected sites by the
 //               MRT collision.
 // A launch costs 4 to 6 us of a step here (latency, not work): with the
@@ -1149,7 +1149,7 @@ static hipError_t launch_select_t(const SelectArgs& a, hipStream_t s) {
   const int nchunk = (int)((tiles * 4 + kSweepRegions - 1) / kSweepRegions);
   const TailArgs t{a.k, a.n_sites, a.selected, a.blist, a.bcap, a.n_sel_out, a.tape_sel,
                    a.tape_cnt, a.tape_len, a.segsel, a.coarse, nchunk};
-  if (nchunk == 1) {
+  if (select_one(tiles * 4, !A.no_carry)) {
     auto one = A.no_carry ? k_sel_one<S, Q, false> : k_sel_one<S, Q, true>;
     hipLaunchKernelGGL(one, dim3(1), dim3(1024), 0, s, A, t);
   } else {
