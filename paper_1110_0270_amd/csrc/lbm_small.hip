@@ -21,20 +21,42 @@
 namespace lbm {
 
 constexpr int kSmallThreads = 1024;
-// Lists of up to this many candidates are ranked by counting; longer ones
-// (the steps without a raised floor) by bisection on the key's bits.
-constexpr int kSmallRank = 512;
+// Lists of up to this many candidates are ranked by counting, longer ones by an
+// MSD radix select.  800 sites FP64, us a step, counting -> radix: k = 8 (16 to
+// 28 candidates) 4.9 either way, k = 12 6.1 -> 5.6, k = 20 8.1 -> 5.8, k = 79
+// 20.4 -> 6.1.  (A bisection on the key's bits, with three barriers a bit, took
+// 37 to 61 us for lists above 512, k above 170 or beyond a tenth of the lattice,
+// more than the 23 to 25 of the step and selection kernels; radix 4.9 to 13.1 at
+// 300 to 4000 sites.)
+constexpr int kSmallRank = 32;
 
-// Number of threads' flags set, over the workgroup; every thread calls it.
-__device__ __forceinline__ int block_count(int mine, int* acc) {
-  __syncthreads();
-  if (threadIdx.x == 0) *acc = 0;
-  __syncthreads();
+// Bin of a 256-bin LDS histogram where the count from the top reaches `need`
+// (at least 1, at most the total): the bin, the count above it and its own.
+// Every thread calls it, after a barrier that ends the histogram's updates.
+// Out of line: inlined twice it cost the short lists' path 6 % (tube of 800
+// sites, 400 steps: 1246 against 1177 us).
+struct SmallBin { int bin; unsigned int above, count; };
+__device__ __noinline__ SmallBin find_small(const unsigned int* h, unsigned int need, SmallBin* out) {
+  if (threadIdx.x < 64) {
+    const int lane = (int)threadIdx.x, top = 255 - 4 * lane;
+    unsigned int c[4], sum = 0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-  if (__lane_id() == 0 && mine) atomicAdd(acc, mine);
+    for (int j = 0; j < 4; ++j) { c[j] = h[top - j]; sum += c[j]; }
+    unsigned int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned int v = __shfl_up(incl, o);
+      if (lane >= o) incl += v;
+    }
+    unsigned int above = incl - sum;
+    if (above < need && need <= incl) {
+      int j = 0;
+      while (above + c[j] < need) above += c[j++];
+      *out = SmallBin{top - j, above, c[j]};
+    }
+  }
   __syncthreads();
-  return *acc;
+  return *out;
 }
 
 template <class S, int SPT>
@@ -49,7 +71,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const StepArgs<typename
   __shared__ uint16_t c_site[CAP];
   __shared__ uint8_t taken[CAP];
   __shared__ unsigned int s_nc;
-  __shared__ int s_acc;
+  __shared__ unsigned int dh[256];
+  __shared__ SmallBin s_bin;
   __shared__ unsigned int s_nsel;
   __shared__ unsigned long long s_kth;    // the key that the next floor takes
   __shared__ unsigned long long s_top[2]; // largest finite key, per parity
@@ -168,7 +191,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const StepArgs<typename
       const long long aim = (raises && !keep && nc >= 3 * a.k) ? 3 * a.k : 0;   // rank, from 1
       const bool last = t + 1 == a.steps;
       const int take = (int)(a.k < nc ? a.k : nc);
-      if (nc <= kSmallRank) {
+      if (__builtin_expect(nc <= kSmallRank, 1)) {
         // rank of each entry: how many beat it (key, then the lower site)
         for (int q = tid; q < nc; q += kSmallThreads) {
           const K key = c_key[q];
@@ -181,40 +204,50 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(const StepArgs<typename
         }
         __syncthreads();
       } else {
-        // the rank-th largest key: its bits from the top
-        auto kth = [&](long long rank, int& above) {
-          K p = 0;
-          above = 0;
-          for (int b = (int)sizeof(K) * 8 - 2; b >= 0; --b) {
-            const K cand = p | ((K)1 << b);
-            int c = 0;
-            for (int q = tid; q < nc; q += kSmallThreads) c += c_key[q] >= cand ? 1 : 0;
-            if (block_count(c, &s_acc) >= rank) p = cand;
+        // the rank-th entry by (key descending, site ascending): digits of the
+        // key from the top, then (sites) those of ~site.  Ends where a digit's
+        // bin is taken whole: for distinct keys after three or four.
+        auto nth = [&](long long rank, bool sites, K& pk, unsigned int& ps) {
+          constexpr int KD = (int)sizeof(K);
+          pk = 0;
+          ps = 0;
+          unsigned int need = (unsigned int)rank;
+          for (int d = 0; d < KD + (sites ? 2 : 0); ++d) {
+            const bool on_key = d < KD;
+            const int sh = 8 * (on_key ? KD - 1 - d : 1 - (d - KD));
+            if (tid < 256) dh[tid] = 0;
+            __syncthreads();
+            for (int b = 0; b < nc; b += kSmallThreads) {
+              const int q = b + tid;
+              bool on = false;
+              unsigned int digit = 0;
+              if (q < nc) {
+                const K key = c_key[q];
+                const unsigned int ns = 0xffffu - c_site[q];
+                on = on_key ? d == 0 || ((key ^ pk) >> (sh + 8)) == 0
+                            : key == pk && (d == KD || ((ns ^ ps) >> 8) == 0);
+                digit = on_key ? (unsigned int)(key >> sh) & 255u : (ns >> sh) & 255u;
+              }
+              hist_add(dh, digit, on);
+            }
+            __syncthreads();
+            const SmallBin bin = find_small(dh, need, &s_bin);
+            need -= bin.above;
+            if (on_key) pk |= (K)bin.bin << sh;
+            else ps |= (unsigned int)bin.bin << sh;
+            if (bin.count == need) break;
           }
-          int c = 0;
-          for (int q = tid; q < nc; q += kSmallThreads) c += c_key[q] > p ? 1 : 0;
-          above = block_count(c, &s_acc);
-          return p;
         };
-        int above;
+        K pk;
+        unsigned int ps;
         if (take > 0) {
-          const K p = kth(take, above);
-          // of the entries at p, the take - above of lowest site: the largest
-          // bound `lim` with fewer than that many sites below it
-          const int want = take - above;
-          int lim = 0;
-          for (int b = 12; b >= 0; --b) {
-            const int cand = lim | (1 << b);
-            int c = 0;
-            for (int q = tid; q < nc; q += kSmallThreads) c += (c_key[q] == p && c_site[q] < cand) ? 1 : 0;
-            if (block_count(c, &s_acc) < want) lim = cand;
-          }
+          nth(take, true, pk, ps);
           for (int q = tid; q < nc; q += kSmallThreads)
-            if (c_key[q] > p || (c_key[q] == p && c_site[q] <= lim)) taken[c_site[q]] = 1;
+            if (c_key[q] > pk || (c_key[q] == pk && 0xffffu - c_site[q] >= ps)) taken[c_site[q]] = 1;
         }
         if (aim) {
-          const K p = kth(aim, above);
-          if (tid == 0) s_kth = (unsigned long long)p;
+          nth(aim, false, pk, ps);
+          if (tid == 0) s_kth = (unsigned long long)pk;
         }
         __syncthreads();
       }
