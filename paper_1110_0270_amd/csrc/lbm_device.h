@@ -149,11 +149,12 @@ __device__ __forceinline__ int c1(int a) { return a == 0 ? 4 : 1; }  // 6 w_a
 // h(x) = (1 + x) ln(1 + x) - x, h(-1) = 1; Taylor series for |x| < 0.1.
 // h_series is the series part, x^2 h_poly(x); h_log(x, l) takes
 // l = ln(1 + x) from the caller (so that a sum that also needs ln(1 + x)
-// evaluates it once).
+// evaluates it once).  `brief` (FP32): the value of the form of fewer terms
+// (h_poly_short, lg1p_series_short), the steps above its first one cleared.
 template <class R>
-__device__ __forceinline__ R h_poly(R x);
+__device__ __forceinline__ R h_poly(R x, bool brief = false);
 template <>
-__device__ __forceinline__ double h_poly<double>(double x) {
+__device__ __forceinline__ double h_poly<double>(double x, bool) {
   double acc = 0.0;
 #pragma unroll
   for (int n = 16; n >= 3; --n) {
@@ -163,12 +164,15 @@ __device__ __forceinline__ double h_poly<double>(double x) {
   return acc + 0.5;
 }
 template <>
-__device__ __forceinline__ float h_poly<float>(float x) {
+__device__ __forceinline__ float h_poly<float>(float x, bool brief) {
   // terms up to x^8 (truncation below 4e-8 of the leading term), Horner's
   // rule in fused multiply-adds: sum_{n=2..8} (-1)^n x^(n-2) / (n (n-1))
   float p = 1.0f / 56.0f;
 #pragma unroll
-  for (int n = 7; n >= 2; --n) p = fmaf(p, x, ((n & 1) ? -1.0f : 1.0f) / (float)(n * (n - 1)));
+  for (int n = 7; n >= 2; --n) {
+    if (n == 5 && brief) p = 0.0f;
+    p = fmaf(p, x, ((n & 1) ? -1.0f : 1.0f) / (float)(n * (n - 1)));
+  }
   return p;
 }
 // FP32, |x| < 0.01: the terms up to x^3 (n <= 5); the rest of the series is
@@ -178,13 +182,13 @@ __device__ __forceinline__ float h_poly_short(float x) {
   return fmaf(fmaf(fmaf(-1.0f / 20.0f, x, 1.0f / 12.0f), x, -1.0f / 6.0f), x, 0.5f);
 }
 template <class R>
-__device__ __forceinline__ R h_series(R x) { return h_poly<R>(x) * x * x; }
+__device__ __forceinline__ R h_series(R x, bool brief = false) { return h_poly<R>(x, brief) * x * x; }
 // Branch-free selects: both forms are evaluated and one is kept, so that the
 // nine components of a site interleave instead of running as nine divergent
 // branches one after another.
 template <class R>
-__device__ __forceinline__ R h_log(R x, R l) {
-  const R ser = h_series<R>(x);
+__device__ __forceinline__ R h_log(R x, R l, bool brief = false) {
+  const R ser = h_series<R>(x, brief);
   const R lgv = (R(1) + x) * l - x;
   return fabs(x) < R(0.1) ? ser : (x <= R(-1) ? R(1) : lgv);
 }
@@ -195,27 +199,30 @@ __device__ __forceinline__ R h_log(R x, R l) {
 // about floating-point arithmetic, 1991, theorem 4): a few units in the last
 // place, against the several hundred instructions of the extended-precision
 // library routine.
-template <class R> __device__ __forceinline__ R lg1p(R x);
-template <> __device__ __forceinline__ double lg1p<double>(double x) { return log1p(x); }
+template <class R> __device__ __forceinline__ R lg1p(R x, bool brief = false);
+template <> __device__ __forceinline__ double lg1p<double>(double x, bool) { return log1p(x); }
 // The series part of lg1p<float> (|x| < 0.1).
-template <class R> __device__ __forceinline__ R lg1p_series(R x);
-template <> __device__ __forceinline__ float lg1p_series<float>(float x) {
+template <class R> __device__ __forceinline__ R lg1p_series(R x, bool brief = false);
+template <> __device__ __forceinline__ float lg1p_series<float>(float x, bool brief) {
   // x sum_{n=1..8} (-1)^(n+1) x^(n-1) / n by Horner's rule in fused
   // multiply-adds
   float p = -1.0f / 8.0f;
 #pragma unroll
-  for (int n = 7; n >= 1; --n) p = fmaf(p, x, ((n & 1) ? 1.0f : -1.0f) / (float)n);
+  for (int n = 7; n >= 1; --n) {
+    if (n == 4 && brief) p = 0.0f;
+    p = fmaf(p, x, ((n & 1) ? 1.0f : -1.0f) / (float)n);
+  }
   return p * x;
 }
-template <> __device__ __forceinline__ double lg1p_series<double>(double x) { return log1p(x); }
+template <> __device__ __forceinline__ double lg1p_series<double>(double x, bool) { return log1p(x); }
 // |x| < 2^-8: the terms to x^4 (the next is below 5e-11 relative, under half
 // a unit in the last place).
 __device__ __forceinline__ float lg1p_series_short(float x) {
   return fmaf(fmaf(fmaf(-1.0f / 4.0f, x, 1.0f / 3.0f), x, -1.0f / 2.0f), x, 1.0f) * x;
 }
 constexpr float kShortSeries = 0x1p-8f;
-template <> __device__ __forceinline__ float lg1p<float>(float x) {
-  const float ser = lg1p_series<float>(x);
+template <> __device__ __forceinline__ float lg1p<float>(float x, bool brief) {
+  const float ser = lg1p_series<float>(x, brief);
   const float u = 1.0f + x;
   const float lgv = __logf(u) * (x * __builtin_amdgcn_rcpf(u - 1.0f));
   return fabsf(x) < 0.1f ? ser : lgv;
@@ -264,14 +271,18 @@ __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 // of S_f in alpha around a.  FP32 keeps T_1..T_3, FP64 T_1..T_10.
 // m = max_i |D_i| / f_i (FP32; from rf): a m < 0.0999999 guarantees every
 // computed |x_i| = |fl(fl(a D_i) rf_i)| < 0.1 (the margin of 1e-6 covers
-// the two roundings), so that the wavefront can take the series alone;
-// below 2^-8 it takes their first terms.
+// the two roundings), so that the wavefront can take the series alone, the
+// values that the other form's selects keep.
 // x_i = a D_i / f_i: in FP32 a D_i times rf_i = rcp(f_i), the value fdiv
 // gives, with the reciprocal taken once per site instead of once per
 // evaluation; in FP64 the correctly rounded quotient, and rf is not read (it
 // may be null).
-// SHORT (FP32): the kernel expects resolved flows and carries the short
-// series.
+// SHORT (FP32): the kernel expects resolved flows, and a site with a m < 2^-8
+// takes the first terms of the series.  They round differently from the whole
+// series about once in 10^4 values, so the site alone decides: a wavefront
+// whose every site is such a one evaluates those terms only, any other clears
+// the steps above them for these sites (`brief`), and a site's result does
+// not depend on the others of its wavefront.
 template <class R> struct ElbmSeries { static constexpr int T = sizeof(R) == 4 ? 3 : 10; };
 template <class R, int Q, bool SHORT>
 __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[Q], R s1, R m,
@@ -304,7 +315,8 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
       rmax = fmax(rmax, fabs(r));
     }
   };
-  if (SHORT && wave_all(a * m < R(kShortSeries))) {
+  const bool brief = SHORT && a * m < R(kShortSeries);
+  if (SHORT && wave_all(brief)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const R x = x_of(i);
@@ -318,8 +330,8 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const R x = x_of(i);
-      s0 += f[i] * h_series<R>(x);
-      t1 += D[i] * lg1p_series<R>(x);
+      s0 += f[i] * h_series<R>(x, brief);
+      t1 += D[i] * lg1p_series<R>(x, brief);
       higher(i);
     }
   } else {
@@ -327,8 +339,8 @@ __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[
     for (int i = 0; i < Q; ++i) {
       const R x = x_of(i);
       const R xl = x < R(-1) ? R(-1) : x;
-      const R l = lg1p<R>(xl);
-      s0 += f[i] * h_log<R>(x, l);
+      const R l = lg1p<R>(xl, brief);
+      s0 += f[i] * h_log<R>(x, l, brief);
       t1 += D[i] * l;
       higher(i);
     }
@@ -395,15 +407,16 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q
   }
   // s1 = sum_i D_i ln(f_i / f*_i), ln(f_i / f*_i) = ln(1 + x_i)
   R s1 = R(0);
-  if (SHORT && wave_all(xabs < R(kShortSeries))) {
+  const bool brief = SHORT && xabs < R(kShortSeries);
+  if (SHORT && wave_all(brief)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) s1 += D[i] * (R)lg1p_series_short((float)x[i]);
   } else if (sizeof(R) == 4 && wave_all(xabs < R(0.1))) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) s1 += D[i] * lg1p_series<R>(x[i]);
+    for (int i = 0; i < Q; ++i) s1 += D[i] * lg1p_series<R>(x[i], brief);
   } else {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) s1 += D[i] * lg1p<R>(x[i]);
+    for (int i = 0; i < Q; ++i) s1 += D[i] * lg1p<R>(x[i], brief);
   }
   R nrm = R(0);
   if (p.norm == 0) {

@@ -304,7 +304,9 @@ void k_step(const StepArgs<typename StoreT<S>::R> A) {
 // and with ROWS > 1 every thread issues the loads of its next row before it
 // computes the current one (two rows of loads in flight per wavefront).
 // Per-site arithmetic is the one-site kernel's, so the results are
-// bit-identical.  Used for the 16-bit storage forms and for ELBM in FP32,
+// bit-identical, but for FP32 ELBM's: there sites near equilibrium take the
+// first terms of the series (SHORT), whose roundings differ about once in 10^4
+// values, with no larger error against 64 bits.  Used for the 16-bit storage forms and for ELBM in FP32,
 // with a compile-time variant without the Ehrenfest code.  16-bit LBGK is
 // held to 64 registers (eight wavefronts per SIMD; the Ehrenfest variant
 // would take 65 and run seven): three spilled values cost less than the
