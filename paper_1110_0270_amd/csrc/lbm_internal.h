@@ -97,7 +97,7 @@ constexpr int kEnsSlots = 64;
 // the lattice (lbm_step3.hip): all zero between steps but for `dense`.
 constexpr int kMed3Groups = 16;
 struct Med3State {
-  unsigned long long tally;  // second kernel: groups done, and (high half) chunks with a candidate
+  unsigned long long tally;  // second kernel: groups done, and (high half) the chunks counted
   int dense;                 // the next step goes to the second kernel alone
   int pad[29];
   unsigned long long group[kMed3Groups][16];   // the same of a group's workgroups, a line each

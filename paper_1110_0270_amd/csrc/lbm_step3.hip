@@ -16,8 +16,11 @@
 //   Delta S is evaluated once per column, not once per neighbour.
 // Where most chunks hold such a site the first kernel would be waste: a step
 // that finds more than a quarter of the chunks flagged leaves the next one to
-// k_step3_median alone, until fewer than an eighth hold a candidate (Med3State;
-// the result does not depend on it).  The first kernel's empty launch then
+// k_step3_median alone, until fewer than an eighth hold a site above 7/8 delta
+// (Med3State; the result does not depend on it).  That kernel has Delta S, not
+// the bound that flags; at 7/8 it counts what the bound would flag while
+// max (f*_i - f_i) / f*_i <= 0.2 (the bound is within 1 + 2/3 of that), so the
+// mode does not change back and forth over a flow just under delta.  The first kernel's empty launch then
 // costs 17 us; with delta = 0 every site off its equilibrium is a candidate,
 // and it is not launched.  256^3 FP32 Taylor-Green vortex, us a step: 1104 ->
 // 694 at delta = 1e-3 (no site above it), 1156 -> 1176 at 1e-9 (all above it),
@@ -61,6 +64,7 @@ __device__ __forceinline__ void finish27(const StepArgs<typename StoreT<S>::R>& 
 }
 
 constexpr int kM3X = 64, kM3Y = 8;
+constexpr double kM3Near = 0.875;
 // Every site off its equilibrium is a candidate: the first kernel is not launched
 template <class R>
 __host__ __device__ inline bool med3_always(R delta) { return !(delta > R(0)); }
@@ -138,7 +142,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
   constexpr bool SH = StoreT<S>::shifted;
   constexpr int NT = TX * TY, SW = TX + 2, NS = (TX + 2) * (TY + 2);
   __shared__ R ring[3][NS];
-  __shared__ int s_had;   // a candidate in this chunk (not a register of the march)
+  __shared__ int s_near;   // a site near delta or above it in this chunk (not a register of the march)
 
   // Workgroup -> (tile, chunk of layers).  Consecutive workgroups are dealt
   // round-robin to the 8 XCDs; each XCD takes a contiguous band of tiles
@@ -158,10 +162,10 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
   // Every workgroup reads the mode before it takes its ticket, so the last
   // one may change it; it and the chunk's record are read again after the
   // march, not kept.  Tickets are 64-bit atomics (workgroups done in the low
-  // half, chunks with a candidate in the high), taken in groups: a thousand on
+  // half, chunks flagged or near delta in the high), taken in groups: a thousand on
   // one address, after two dependent loads, cost 11 us of a 705 us step
   // (256^3 FP32).
-  auto leave = [&](bool had, bool dense, bool flagged, unsigned long long pos) {
+  auto leave = [&](bool near, bool dense, bool flagged, unsigned long long pos) {
     if (tid != 0) return;
     // the first kernel's positivity events stand where this one did nothing
     Med3Chunk* const chunk_st = med3_chunk(A.med3) + tb;
@@ -169,7 +173,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     if (pos) chunk_st->pos_events = 0ull;
     if (flagged) chunk_st->flag = 0ull;
     const int g = tb % kMed3Groups;
-    const unsigned long long mine = 1ull | ((had ? 1ull : 0ull) << 32);
+    const unsigned long long mine = 1ull | (((dense ? near : flagged) ? 1ull : 0ull) << 32);
     const unsigned long long in_g = atomicAdd(&A.med3->group[g][0], mine) + mine;
     if ((unsigned int)in_g != (unsigned int)((T - g + kMed3Groups - 1) / kMed3Groups)) return;
     A.med3->group[g][0] = 0ull;
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
       leave(false, false, false, pos);
       return;
     }
-    if (tid == 0) s_had = 0;   // the first layer's barrier is before the first candidate
+    if (tid == 0) s_near = 0;   // the first layer's barrier is before the first vote
   }
 
   // Delta S of layer z (periodic) over the tile and its halo into ring slot
@@ -230,8 +234,10 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
       const int dz = k / 9 - 1, dy = (k / 3) % 3 - 1, dx = k % 3 - 1;
       return ring[dz < 0 ? sm : (dz > 0 ? sp : sc)][(ly + 1 + dy) * SW + lx + 1 + dx];
     };
+    if constexpr (!ALL) {
+      if (__ballot(valid && !(dS <= A.med_delta * R(kM3Near)))) s_near = 1;
+    }
     if (__ballot(cand)) {
-      if constexpr (!ALL) s_had = 1;
       int below = 0;
 #pragma unroll
       for (int k = 0; k < 27; ++k) below += nbr(k) < dS ? 1 : 0;
@@ -261,7 +267,7 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
     __syncthreads();   // the next layer overwrites the ring slot of z - 1
   }
   if constexpr (!ALL)
-    leave(s_had != 0, A.med3->dense != 0, med3_chunk(A.med3)[tb].flag != 0,
+    leave(s_near != 0, A.med3->dense != 0, med3_chunk(A.med3)[tb].flag != 0,
           med3_chunk(A.med3)[tb].pos_events);
 }
 
