@@ -108,6 +108,7 @@ struct Med3Chunk {
 };
 __host__ __device__ inline Med3Chunk* med3_chunk(Med3State* m) { return reinterpret_cast<Med3Chunk*>(m + 1); }
 long long med3_chunks(int storage, int nx, int ny, int nz);
+bool step3_screens(int nx, int ny, int nz);
 
 template <class R> struct KeyOf;
 template <> struct KeyOf<float> { using T = uint32_t; };

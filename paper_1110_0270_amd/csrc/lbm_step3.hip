@@ -133,8 +133,8 @@ __device__ __forceinline__ R median27(R a[27]) {
   return a[13];
 }
 
-// ALL: every chunk is taken (med3_always), without the first kernel and its
-// records.
+// ALL: every chunk is taken (med3_always, or rows past the first kernel's
+// launch), without the first kernel and its records.
 template <class S, int TX, int TY, int ZC, bool ALL>
 __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX * TY <= 512) ? 4 : 1) void k_step3_median(const StepArgs<typename StoreT<S>::R> A,
                                                           int tiles_x, int tiles_y) {
@@ -272,12 +272,21 @@ __global__ __launch_bounds__(TX * TY, (sizeof(typename StoreT<S>::R) == 4 && TX 
 }
 
 // ---------------------------------------------------------------------------
+// Workgroups of the row kernels (k_step3), and whether the median step may use
+// them: a launch holds fewer than 2^32 threads, and a narrow lattice pays 256
+// of them for each of its rows (64 x 2^12 x 2^12 sites: 2^24 rows).  The
+// marching kernel's 512 take 8 rows of 16 or 32 layers.
+static long long step3_row_groups(int nx, int ny, int nz) {
+  return (nx + 255) / 256 * (long long)ny * nz;
+}
+bool step3_screens(int nx, int ny, int nz) { return step3_row_groups(nx, ny, nz) * 256 < (1ll << 32); }
+
 template <class S>
 static hipError_t launch3(bool median, const void* args, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
   using R = typename StoreT<S>::R;
   const StepArgs<R>& A = *(const StepArgs<R>*)args;
-  const dim3 rows((unsigned)((A.nx + 255) / 256 * (long long)A.ny3 * A.nz));
+  const dim3 rows((unsigned)step3_row_groups(A.nx, A.ny3, A.nz));
   if (median) {
     // 64 x 8 columns: 1.29 halo sites per site (FP32 arithmetic: 64 x 16
     // tiles measured no faster)
@@ -288,7 +297,7 @@ static hipError_t launch3(bool median, const void* args, hipStream_t s, hipEvent
     auto second = k_step3_median<S, kM3X, kM3Y, ZC, false>;
     auto alone = k_step3_median<S, kM3X, kM3Y, ZC, true>;
     if (e0) (void)hipEventRecord(e0, s);
-    if (med3_always(A.med_delta)) {
+    if (med3_always(A.med_delta) || !step3_screens(A.nx, A.ny3, A.nz)) {
       hipLaunchKernelGGL(alone, grid, block, 0, s, A, tx, ty);
     } else {
       hipLaunchKernelGGL(first, rows, dim3(256), 0, s, A);
