@@ -149,7 +149,12 @@ typedef struct lbm_config {
   int elbm_norm;          /* LBM_NORM_*                                         */
   int elbm_fallback;      /* no-root rule: LBM_FB_POSITIVITY | LBM_FB_EHRENFEST  */
   double elbm_eps;        /* stop when |S_f/S_f'| * ||Delta|| < eps (1e-14)     */
-  int elbm_max_iter;      /* parabola iterations (32)                           */
+  int elbm_max_iter;      /* parabola iterations (32).  LBM_F64, lattices of more
+                             than 65536 sites (fewer if ragged): a site with
+                             max |Delta_i| / f_i < 2^-5 takes its root to FP64
+                             rounding from a series, whatever elbm_norm,
+                             elbm_eps and elbm_max_iter say, and counts as one
+                             iteration                                          */
   double elbm_dS_cut;     /* Delta S below this: plain LBGK (1e-15)             */
   double elbm_f64_below;  /* FP32 modes: sites with alpha_max below this bound
                              solve the root in FP64 (3.0)                      */

@@ -70,11 +70,11 @@ hipError_t launch_adjoint(int storage, int Q, int coll, const void* step_args, c
                           const void* alpha, const unsigned char* branch, const int32_t* list,
                           const long long* count, long long k, const MedianAdjoint& med,
                           hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-// f* written into step_args->dst at the first *count sites of list (<= k).
 // The recompute's step (LBGK, MRT; no median filter, no MRT limiter) with the
 // recorded sites of a short list (k <= kAdjListMax) sent to f*.
 hipError_t launch_restep(int storage, int Q, int coll, const void* step_args, const int32_t* list,
                          const long long* count, long long k, hipStream_t s);
+// f* written into step_args->dst at the first *count sites of list (<= k).
 hipError_t launch_tape_fix(int storage, int Q, const void* step_args, const int32_t* list,
                            const long long* count, long long k, hipStream_t s);
 hipError_t launch_mark(unsigned char* mask, const int32_t* list, const long long* count,

@@ -290,6 +290,13 @@ void fill_args(StepArgs<R>& A, const lbm_config* c, const Layout& L, char* ws) {
   A.eps64 = c->elbm_eps;
   A.dS_cut64 = c->elbm_dS_cut;
   A.f64_below = (R)c->elbm_f64_below;
+  // One workgroup per compute unit or fewer is one wavefront per SIMD, and
+  // beside a wall it holds both near and other sites: the two roots in turn
+  // took 29-32 us a step where the iteration for all takes 15.5-18 (64^2 to
+  // 256^2, cavity and diffusive walls; 20-25 before either).  With more, the
+  // series makes room for the others: 300^2 30.7 -> 24.5-25 us, 512^2 39 ->
+  // 24-32, 2048^2 511 -> 235.
+  A.near_series = (long long)A.tiles_x * A.tiles_y > 256 ? 1 : 0;
   A.med_delta = (R)c->med_delta;
   A.ehr_delta = (R)c->ehr_delta;
   A.sel = (SelState*)(ws + L.off_sel);

@@ -228,18 +228,13 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
     bool f64 = false;
     // m = max |D_i| / f_i
     R rf[Q], m = R(0), fmin_ = fa[0];
+    if constexpr (sizeof(R) == 4) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      fmin_ = fmin(fmin_, fa[i]);
-      if constexpr (sizeof(R) == 4) {
+      for (int i = 0; i < Q; ++i) {
+        fmin_ = fmin(fmin_, fa[i]);
         rf[i] = rcp<R>(fa[i]);
         m = fmax(m, fabs(d[i]) * rf[i]);
-      } else {
-        rf[i] = d[i] / fa[i];
-        m = fmax(m, fabs(rf[i]));
       }
-    }
-    if constexpr (sizeof(R) == 4) {
       // alpha_max >= 1/m, which settles every test against alpha_max near
       // equilibrium without its nine quotients
       bool lower = false;
@@ -273,7 +268,17 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
         alpha = elbm_alpha<R, Q, SHORT>(fa, qa, d, rf, m, amax, lower, ep, br, ci.iters);
       }
     } else {
-      if (fmin_ > R(0) && m < kElbmNear)
+      bool near = false;
+      if (A.near_series) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          fmin_ = fmin(fmin_, fa[i]);
+          rf[i] = d[i] / fa[i];
+          m = fmax(m, fabs(rf[i]));
+        }
+        near = fmin_ > R(0) && m < kElbmNear;
+      }
+      if (near)
         alpha = elbm_alpha_near<Q>(qa, d, rf, A.dS_cut, br, ci.iters);
       else
         alpha = elbm_alpha<R, Q>(fa, qa, d, rf, m, alpha_max<R, Q>(fa, d), false, ep, br, ci.iters);

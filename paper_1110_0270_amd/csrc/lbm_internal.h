@@ -144,6 +144,7 @@ struct StepArgs {
   // ELBM
   R eps, atol, dS_cut;
   int max_iter, norm, fallback;
+  int near_series;       // FP64: sites near equilibrium take elbm_alpha_near
   double eps64, dS_cut64;
   R f64_below;
   // median

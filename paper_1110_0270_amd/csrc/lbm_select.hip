@@ -75,7 +75,10 @@ __device__ __forceinline__ void st_dev(T* p, T v) {
 // device-scope release (each one writes back its XCD's whole L2, which held up
 // 256 of them: the two launches of a rescan took 196 and 490 us at 4096^2 with
 // them, 130 and 330 without; 86 and 155, 27 and 50 at 1500 x 1001).
-// The last workgroup drops what its own caches hold of those lines.
+// The last workgroup drops what its own caches hold of those lines.  Nothing
+// here orders a plain store before the ticket: all that the last workgroup reads
+// of the others' must be written by st_dev or an atomic, and a plain store
+// added to what leads here would break it.
 __device__ __forceinline__ bool last_block(unsigned int* ticket) {
   __shared__ bool is_last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
