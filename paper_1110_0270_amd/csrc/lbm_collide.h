@@ -27,7 +27,7 @@ __device__ __noinline__ ElbmF64Result elbm_alpha_fp64(ElbmF64Site s, double eps,
   }
   ElbmParams<double> e64{eps, 0.0, dS_cut, max_iter, norm, fallback};
   ElbmF64Result r;
-  r.alpha = (float)elbm_alpha<double, Q>(fd, qd, Dd, nullptr, 0.0, alpha_max<double, Q>(fd, Dd),
+  r.alpha = (float)elbm_alpha<double, Q, false, false, 1>(fd, qd, Dd, nullptr, 0.0, alpha_max<double, Q>(fd, Dd),
                                          false, e64, r.branch, r.iters);
   return r;
 }
@@ -229,11 +229,14 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
     // m = max |D_i| / f_i
     R rf[Q], m = R(0), fmin_ = fa[0];
     if constexpr (sizeof(R) == 4) {
+      constexpr bool OWN = !SHORT && !DEFER;
+      if constexpr (!OWN) {
 #pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        fmin_ = fmin(fmin_, fa[i]);
-        rf[i] = rcp<R>(fa[i]);
-        m = fmax(m, fabs(d[i]) * rf[i]);
+        for (int i = 0; i < Q; ++i) {
+          fmin_ = fmin(fmin_, fa[i]);
+          rf[i] = rcp<R>(fa[i]);
+          m = fmax(m, fabs(d[i]) * rf[i]);
+        }
       }
       // alpha_max >= 1/m, which settles every test against alpha_max near
       // equilibrium without its nine quotients
@@ -265,7 +268,7 @@ __device__ __forceinline__ void collide_site(const StepArgs<typename StoreT<S>::
         ci.iters = r.iters;
         f64 = true;
       } else {
-        alpha = elbm_alpha<R, Q, SHORT>(fa, qa, d, rf, m, amax, lower, ep, br, ci.iters);
+        alpha = elbm_alpha<R, Q, SHORT, OWN>(fa, qa, d, rf, m, amax, lower, ep, br, ci.iters);
       }
     } else {
       bool near = false;

@@ -268,7 +268,8 @@ __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 // same for every alpha.  With r_i = D_i / (f_i + a D_i) the higher
 // derivatives are S_f^(n+1) = (-1)^n (n-1)! T_n, T_n = sum D_i r_i^n, n >= 1;
 // rmax = max |r_i| bounds the ratio of consecutive terms of the Taylor series
-// of S_f in alpha around a.  FP32 keeps T_1..T_3, FP64 T_1..T_10.
+// of S_f in alpha around a.  NT of them are kept: T_1..T_3 in FP32, T_1..T_10
+// in FP64, T_1 alone where the later iterates take no series.
 // m = max_i |D_i| / f_i (FP32; from rf): a m < 0.0999999 guarantees every
 // computed |x_i| = |fl(fl(a D_i) rf_i)| < 0.1 (the margin of 1e-6 covers
 // the two roundings), so that the wavefront can take the series alone, the
@@ -283,11 +284,9 @@ __device__ __forceinline__ bool wave_all(bool b) { return __all(b) != 0; }
 // whose every site is such a one evaluates those terms only, any other clears
 // the steps above them for these sites (`brief`), and a site's result does
 // not depend on the others of its wavefront.
-template <class R> struct ElbmSeries { static constexpr int T = sizeof(R) == 4 ? 3 : 10; };
-template <class R, int Q, bool SHORT>
+template <class R, int Q, bool SHORT, int NT>
 __device__ __forceinline__ void sf_parts(const R f[Q], const R rf[Q], const R D[Q], R s1, R m,
-                                         R a, R& sf, R& d1, R T[ElbmSeries<R>::T], R& rmax) {
-  constexpr int NT = ElbmSeries<R>::T;
+                                         R a, R& sf, R& d1, R T[NT], R& rmax) {
   R s0 = R(0), t1 = R(0);
 #pragma unroll
   for (int n = 0; n < NT; ++n) T[n] = R(0);
@@ -382,8 +381,14 @@ struct ElbmParams {
 // FP32: rf = rcp(f), m = max_i |D_i| / f_i (FP64 reads neither).  `lower` says that amax is only a
 // lower bound of alpha_max; the exact value is taken where the bound does not
 // settle a decision (the decisions, and so alpha, are those of the exact one).
-template <class R, int Q, bool SHORT = false>
-__device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q], R m, R amax,
+// OWN: rf and m are formed here, past the cutoff, and the caller's not read (a
+// kernel with the FP64 root out of line has no registers to hold them).
+// NT = 1: no Taylor series between the evaluations (the root out of line: its
+// ten terms took the median kernel from 243 registers a lane to 265 and from
+// two wavefronts a SIMD to one; 1100 x 700 FP32 Couette 96 us a step, 52
+// without them and with OWN).
+template <class R, int Q, bool SHORT = false, bool OWN = false, int NT = sizeof(R) == 4 ? 3 : 10>
+__device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R* rf_, R m, R amax,
                         bool lower, const ElbmParams<R>& p, int& branch, int& iters) {
   iters = 0;
   bool nonpos = false;
@@ -425,6 +430,16 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q
 #pragma unroll
     for (int i = 0; i < Q; ++i) nrm += fabs(D[i]);
   }
+  R rf_own[Q];
+  if constexpr (OWN && sizeof(R) == 4) {
+    m = R(0);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      rf_own[i] = rcp<R>(f[i]);
+      m = fmax(m, fabs(D[i]) * rf_own[i]);
+    }
+  }
+  const R* const rf = OWN ? rf_own : rf_;
   // One evaluation site for S_f and its derivatives (the kernel's code size
   // decides its speed).  A root exists iff S_f(alpha_max) < 0 (alpha_max
   // finite).  S_f is concave (S is concave, f + alpha D affine) with
@@ -443,7 +458,6 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q
   // |dl| rmax <= 2^-5 (omitted: below 2^-50 of the second-order term); the
   // logarithms of a second and third evaluation bound the walls' wavefronts
   // (256^2 cavity).
-  constexpr int NT = ElbmSeries<R>::T;
   constexpr R kReach = sizeof(R) == 4 ? R(0x1p-10) : R(0x1p-5);
   bool need_probe = amax < r_inf<R>();
   bool saved = false, full = true;
@@ -463,7 +477,7 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q
     const bool probing = need_probe && saved;
     if (full || probing) {
       R e0, e1, eT[NT], em;
-      sf_parts<R, Q, SHORT>(f, rf, D, s1, m, probing ? amax : a, e0, e1, eT, em);
+      sf_parts<R, Q, SHORT, NT>(f, rf, D, s1, m, probing ? amax : a, e0, e1, eT, em);
       if (probing) {
         if (e0 >= R(0)) {
           branch = EB_NOROOT;
@@ -542,7 +556,7 @@ __device__ R elbm_alpha(const R f[Q], const R feq[Q], const R D[Q], const R rf[Q
     if (an >= amax) an = R(0.5) * (a + amax);
     if (an <= R(1)) an = R(0.5) * (a + R(1));
     a = an;
-    full = !(fabs(a - c) * rmax <= kReach);
+    full = NT == 1 || !(fabs(a - c) * rmax <= kReach);
   }
   branch = EB_ROOT;
   return a;
