@@ -251,13 +251,15 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 // Lattices (regions: four per tile) whose selection is one workgroup's, in one
 // launch.  A carried selection may have to rescan the lattice (one step in 40
 // to 100 of a shear layer's first 384, several in its first 64), and with one
-// workgroup a rescan's time grows with the lattice; the second launch costs 5
-// us every step.  Shear layers, us a step over the first 64, one launch -> two
-// (four launches before): 256^2 FP64 53.3 -> 24.9 (30.8), 200^2 FP64 44.5 ->
-// 25.2 (30.9), 250^2 FP32 30.2 -> 23.4 (28.4); 100 x 80 FP64 stays with one,
-// 25.2 (28.3).  Without a floor there is no rescan, and one workgroup serves a
-// whole sweep chunk.
-inline bool select_one(long long regions, bool carried) { return regions <= (carried ? 256 : kSweepRegions); }
+// workgroup a rescan's time grows with the lattice; the second launch costs 1
+// to 2 us every step.  us a step, one launch -> two (four launches before), over
+// the first steps of a set lattice: shear layer 256^2 FP64 53.3 -> 24.9 (30.8);
+// turbulence 120 x 90 FP64 50.5 -> 32.0 (41.2), 70 x 37 FP64 43.1 -> 32.9 (43.0),
+// FP32 29.1 -> 25.8 (37.5); and later on 21.3 -> 22.9 (27.4), 22.1 -> 22.8 (27.9),
+// 20.3 -> 20.9 (26.0).  60 x 60 stays with one, 42.1 and 21.5 (44.1, 27.6).
+// Without a floor there is no rescan, and one workgroup serves a whole sweep
+// chunk.
+inline bool select_one(long long regions, bool carried) { return regions <= (carried ? 64 : kSweepRegions); }
 // Place the first candidate floor of a freshly set lattice at the 3k-th
 // largest Delta S of its next step (one rescan).
 hipError_t launch_select_calibrate(const SelectArgs& a, hipStream_t s);
