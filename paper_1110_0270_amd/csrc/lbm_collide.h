@@ -27,8 +27,8 @@ __device__ __noinline__ ElbmF64Result elbm_alpha_fp64(ElbmF64Site s, double eps,
   }
   ElbmParams<double> e64{eps, 0.0, dS_cut, max_iter, norm, fallback};
   ElbmF64Result r;
-  r.alpha = (float)elbm_alpha<double, Q, false, false, 1>(fd, qd, Dd, nullptr, 0.0, alpha_max<double, Q>(fd, Dd),
-                                         false, e64, r.branch, r.iters);
+  r.alpha = (float)elbm_alpha<double, Q, false, false, 1>(
+      fd, qd, Dd, nullptr, 0.0, alpha_max<double, Q>(fd, Dd), false, e64, r.branch, r.iters);
   return r;
 }
 

@@ -378,9 +378,10 @@ struct ElbmParams {
 // inequality), so sum f*_i x_i^2 / (2 (1 + max x/3)) <= Delta S decides it
 // for every other site.  The same x_i give ln(f_i / f*_i) and the entropic
 // norm.
-// FP32: rf = rcp(f), m = max_i |D_i| / f_i (FP64 reads neither).  `lower` says that amax is only a
-// lower bound of alpha_max; the exact value is taken where the bound does not
-// settle a decision (the decisions, and so alpha, are those of the exact one).
+// FP32: rf_ = rcp(f), m = max_i |D_i| / f_i (FP64 reads neither).  `lower` says
+// that amax is only a lower bound of alpha_max; the exact value is taken where
+// the bound does not settle a decision (the decisions, and so alpha, are those
+// of the exact one).
 // OWN: rf and m are formed here, past the cutoff, and the caller's not read (a
 // kernel with the FP64 root out of line has no registers to hold them).
 // NT = 1: no Taylor series between the evaluations (the root out of line: its
